@@ -113,7 +113,7 @@ typedef struct {
                              instances of the context or batch fit in the
                              256 MB last-level cache, else compacted fused
                              (every instance must then be LBM_AUTO). */
-  int32_t tile_rows;      /* fused D2Q9 tile height: 8, 12 or 16 (0 = 12);
+  int32_t tile_rows;      /* fused D2Q9 tile height: 8, 12 or 16 (0 = the library's choice);
                              for the compacted layouts in 3D, the rows per
                              band of the fluid-node numbering (bands of rows,
                              z-slice by z-slice; 0 = sized from the grid) */

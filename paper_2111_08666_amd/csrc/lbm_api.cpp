@@ -667,7 +667,7 @@ lbm_status create_batch(int32_t k, const lbm_geometry *g, const lbm_params *p,
   // not fit the L2), the fused step otherwise
   int strategy = resolve_strategy(g[0], p[0]);
   b->compact = compact_strategy(strategy);
-  const lbm_status ps = apply_plan(b, strategy, p[0].tile_rows ? p[0].tile_rows : 12);
+  const lbm_status ps = apply_plan(b, strategy, p[0].tile_rows ? p[0].tile_rows : fused_rows(b->storage, b->compact));
   if (ps != LBM_OK) return ps;
   *out = owner.release();
   return LBM_OK;
@@ -1051,7 +1051,12 @@ lbm_status lbm_batch_kernel_info(const lbm_batch *b, char *name, size_t name_len
       *grid_blocks = b->n_blocks;
     }
   }
-  if (block_threads) *block_threads = b->strategy == LBM_COMPACT ? kCompactThreads : 256;
+  if (block_threads) {
+    const bool fused9 = b->q == 9 && (b->strategy == LBM_FUSED || b->strategy == LBM_COMPACT_FUSED);
+    *block_threads = b->strategy == LBM_COMPACT ? kCompactThreads
+                     : fused9 ? 64 * fused_waves(b->ty, b->math == LBM_MATH_F64, b->storage, b->compact)
+                              : 256;
+  }
   return LBM_OK;
 }
 

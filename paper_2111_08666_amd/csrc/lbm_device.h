@@ -20,6 +20,14 @@ constexpr uint32_t kLinkMask = (1u << 19) - 1u;
 // 2D step tile: 64 lanes cover 60 interior columns plus 2 halo columns on
 // each side; TY interior rows (8, 12 or 16) plus 2 halo rows above and below.
 constexpr int kTileX = 60;
+// Waves per block of the fused D2Q9 step (lbm_step.h has the measurements).
+constexpr int fused_waves(int ty, bool f64, int storage, bool compact) {
+  return ty == 8 && !(compact && !(f64 && storage == LBM_STORE_F32)) ? 8 : 4;
+}
+// Tile height of the fused D2Q9 step when none is asked for: 8 rows, but 12
+// on the compacted layout with BF16 storage, whose pulls are the dearest per
+// halo row (24 uneven instances: 109 us per step against 114 with 8).
+constexpr int fused_rows(int storage, bool compact) { return compact && storage != LBM_STORE_F32 ? 12 : 8; }
 // 3D step tile: the same 64-lane rows, TY3 interior rows in y, marching in z.
 constexpr int kTileY3 = 8;
 // Compacted 3D fused step: a tile is one row word (64 columns) by kFwdRows

@@ -432,42 +432,54 @@ __device__ __forceinline__ void ccomplete9(const InstDev &d, gcf *__restrict__ f
 }
 
 // ---------------------------------------------------------------------------
-// D2Q9 fused step.  Block = 4 waves over a region of 64 columns x (TY + 4)
+// D2Q9 fused step.  Block = NW waves over a region of 64 columns x (TY + 4)
 // rows: 60 x TY interior nodes plus a 2-node halo.  Wave w owns interior rows
-// 2 + w + 4k (k < TY/4) and one halo row; a row is wave-uniform, so every pull
-// is one load from a scalar row base plus the lane's x.
+// 2 + w + NW k (k < TY / NW), the first four waves one halo row each; a row is
+// wave-uniform, so every pull is one load from a scalar row base plus the
+// lane's x.
 // Phase 1: pull + complete + densities for all region nodes -> LDS.
 // Phase 2: virtual solid density (Eq. 17) in place at solid region nodes.
 // Phase 3: force (Eq. 13 with the open-face mirror) and collision for the
 //          interior nodes, whose pulled populations stayed in registers.
 // ---------------------------------------------------------------------------
-// Occupancy: the step is bound by the latency of its memory chain, so
-// resident waves count (the 64-instance batch at TY = 12 takes 15 % longer
-// with three blocks per CU than with four, 49 % with two).  TY = 12 parks
-// the last interior row of each wave in LDS between the phases, which fits
-// it in 128 registers and 26 KB of LDS (four waves per SIMD).  With FP32
-// node arithmetic and FP32 storage TY = 8 parks its last row as well and
-// fits 80 registers: six waves per SIMD (measured 5 % faster on the batch
-// and 7 % on a 1024 x 512 instance than four waves with every row in
-// registers); otherwise it keeps every pulled row in registers at four waves.
-template <int TY, typename R, int ST> struct FusedShape {
+// Waves and occupancy.  fused_waves (lbm_device.h) gives the waves of a block:
+// eight, one interior row each, for the 8-row tile, or four with TY / 4 rows
+// each.  A step on a small grid is a serial chain in one wave (instruction
+// fetch of straight-line code, node info and pulls, two barriers, the
+// stencil, the collision, the stores), and on a large one what hides that
+// chain is waves in flight; a wave with one row has a third of the code of
+// one with three and needs no row parked in LDS.  Measured with MRT, us per
+// step at TY = 8 with eight waves against four (and TY = 12 with four):
+// 128 x 64 6.8 / 14.6 (19.7), 401 x 203 in FP64 11.6 / 14.7 (17.7),
+// 1024 x 512 20.1 / 20.8 (23.8), 2000 x 1000 70.4 / 76.0 (75.0), nine
+// 192 x 192 droplets 12.6 / 13.4 (15.3).  The compacted FP32 step keeps four
+// waves (24 uneven instances: 104.9 against 115.1 us): its rank lookups cost
+// more per row than the registers of a second row; in FP64 eight win there
+// too (165 against 188-196).
+// Four waves with TY = 12, and with TY = 8 in FP32, park the last interior row of
+// each wave in LDS between the phases, to fit four and six waves per SIMD.
+template <int TY, typename R, int ST, int CL> struct FusedShape {
   static constexpr bool kF32 = sizeof(R) == 4 && ST == 0;
-  static constexpr int kParked = (TY == 12 || (TY == 8 && kF32)) ? 1 : 0;  // interior rows per wave kept in LDS
-  static constexpr int kWaves = TY == 16 ? 1 : ((TY == 8 && kF32) ? 6 : 4);
+  static constexpr int kNW = fused_waves(TY, sizeof(R) == 8, ST, CL);  // waves per block
+  static constexpr int kRows = TY / kNW;                               // interior rows per wave
+  static constexpr int kParked = (kRows == 3 || (kRows == 2 && kF32)) ? 1 : 0;  // of them kept in LDS
+  static constexpr int kWaves = kRows == 4 ? 1 : ((kRows <= 2 && kF32) ? 6 : 4);
 };
 
 // CL = 1: the same step over the compacted layout (fluid nodes only stored,
 // pulls by rank, bounce-back from the node's own slots, no ghost slots).
 template <int COLL, int ST, typename R, int TY, int CL = 0>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FusedShape<TY, R, ST>::kWaves))) void step_d2q9(
+__global__ __launch_bounds__((64 * FusedShape<TY, R, ST, CL>::kNW))
+    __attribute__((amdgpu_waves_per_eu(FusedShape<TY, R, ST, CL>::kWaves))) void step_d2q9(
     const InstDev *__restrict__ insts, const int32_t *__restrict__ block_inst, int parity) {
   using L = Lat<9>;
   using V = Vec2<R>;
-  constexpr int KR = TY / 4;        // interior rows per wave
+  constexpr int NW = FusedShape<TY, R, ST, CL>::kNW;
+  constexpr int KR = TY / NW;       // interior rows per wave
   constexpr int kRH = TY + 4;       // region rows
-  constexpr int KP = FusedShape<TY, R, ST>::kParked;
+  constexpr int KP = FusedShape<TY, R, ST, CL>::kParked;
   __shared__ V psi[kRH][64];
-  __shared__ float park[KP > 0 ? KP * 4 : 1][18][64];  // [row slot * 4 + wave][component * 9 + link][lane]
+  __shared__ float park[KP > 0 ? KP * NW : 1][18][64];  // [row slot * NW + wave][component * 9 + link][lane]
 
   const int bid = xcd_block_alternating(parity);
   const int inst = __builtin_amdgcn_readfirstlane(block_inst ? block_inst[bid] : 0);
@@ -494,14 +506,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FusedShape<
   int xs[3];
   source_x(d, gxa, xs);
 
-  // rows owned (wave-uniform): k < KR interior (2 + wave + 4k), k = KR halo
+  // rows owned (wave-uniform): k < KR interior (2 + wave + NW k), k = KR the
+  // halo row of the first four waves
+  const bool has_halo = NW == 4 || wave < 4;
   int rows[KR + 1], gy[KR + 1];
   bool row_in[KR + 1];
 #pragma unroll
   for (int k = 0; k <= KR; ++k) {
-    rows[k] = k < KR ? 2 + wave + 4 * k : (wave < 2 ? wave : TY + wave);
+    rows[k] = k < KR ? 2 + wave + NW * k : (wave < 2 ? wave : TY + wave);
     int y = ty * TY - 2 + rows[k];
-    bool in = true;
+    bool in = k < KR || has_halo;
     if (y < 0 || y >= ny) {
       if (py) y = wrap_index(y, ny);
       else in = false;
@@ -535,7 +549,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FusedShape<
 #pragma unroll
     for (int k = 0; k < KR; ++k)
       if (ST == 0 || !(info[k] & kSolid)) pull_row<9, ST>(d, fin, info[k], srow[k], xs, f0[k], f1[k]);
-    if (ST == 0 || !(info[KR] & kSolid)) pull_row<9, ST>(d, fin, info[KR], srow[KR], xs, h0, h1);
+    if (has_halo && (ST == 0 || !(info[KR] & kSolid))) pull_row<9, ST>(d, fin, info[KR], srow[KR], xs, h0, h1);
   }
 #pragma unroll
   for (int k = 0; k <= KR; ++k) {
@@ -555,9 +569,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FusedShape<
       rho1 = (R)h.x;
       rho2 = (R)h.y;
     }
-    psi[rows[k]][lane] = V{rho1, rho2};
+    if (k < KR || has_halo) psi[rows[k]][lane] = V{rho1, rho2};
     if (k >= KR - KP && k < KR) {
-      float(&pk)[18][64] = park[(k - (KR - KP)) * 4 + wave];
+      float(&pk)[18][64] = park[(k - (KR - KP)) * NW + wave];
 #pragma unroll
       for (int i = 0; i < 9; ++i) {
         pk[i][lane] = f0[k < KR ? k : 0][i];
@@ -629,7 +643,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FusedShape<
     const R F1x = -G_ * rho1 * sx2 + rho1 * gxb, F1y = -G_ * rho1 * sy2 + rho1 * gyb;
     const R F2x = -G_ * rho2 * sx1 + rho2 * gxb, F2y = -G_ * rho2 * sy1 + rho2 * gyb;
     if (k >= KR - KP) {
-      const float(&pk)[18][64] = park[(k - (KR - KP)) * 4 + wave];
+      const float(&pk)[18][64] = park[(k - (KR - KP)) * NW + wave];
 #pragma unroll
       for (int i = 0; i < 9; ++i) {
         f0[k][i] = pk[i][lane];
@@ -1763,14 +1777,17 @@ template <int COLL, int ST, typename R>
 static void launch_fused_q(int q, int ty, const InstDev *d, const int32_t *bi, int64_t nb, int parity,
                            hipStream_t s, bool compact = false) {
   const dim3 g((unsigned)nb), b(256);
-  if (q == 9 && compact) {
-    if (ty == 8) step_d2q9<COLL, ST, R, 8, 1><<<g, b, 0, s>>>(d, bi, parity);
-    else if (ty == 16) step_d2q9<COLL, ST, R, 16, 1><<<g, b, 0, s>>>(d, bi, parity);
-    else step_d2q9<COLL, ST, R, 12, 1><<<g, b, 0, s>>>(d, bi, parity);
-  } else if (q == 9) {
-    if (ty == 8) step_d2q9<COLL, ST, R, 8><<<g, b, 0, s>>>(d, bi, parity);
-    else if (ty == 16) step_d2q9<COLL, ST, R, 16><<<g, b, 0, s>>>(d, bi, parity);
-    else step_d2q9<COLL, ST, R, 12><<<g, b, 0, s>>>(d, bi, parity);
+  if (q == 9) {
+    const dim3 bt(64 * fused_waves(ty, sizeof(R) == 8, ST, compact));
+    if (compact) {
+      if (ty == 8) step_d2q9<COLL, ST, R, 8, 1><<<g, bt, 0, s>>>(d, bi, parity);
+      else if (ty == 16) step_d2q9<COLL, ST, R, 16, 1><<<g, bt, 0, s>>>(d, bi, parity);
+      else step_d2q9<COLL, ST, R, 12, 1><<<g, bt, 0, s>>>(d, bi, parity);
+    } else {
+      if (ty == 8) step_d2q9<COLL, ST, R, 8><<<g, bt, 0, s>>>(d, bi, parity);
+      else if (ty == 16) step_d2q9<COLL, ST, R, 16><<<g, bt, 0, s>>>(d, bi, parity);
+      else step_d2q9<COLL, ST, R, 12><<<g, bt, 0, s>>>(d, bi, parity);
+    }
   } else {
     step_d3q19<COLL, ST, R><<<g, b, 0, s>>>(d, bi, parity);
   }
