@@ -518,6 +518,270 @@ __global__ __launch_bounds__(256) void igemm_wgrad(WgradArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Weight gradients with all taps in one block.  A block owns a chunk of pixels
+// and a 32 x 32 tile of (output, input) channels and accumulates every tap of
+// that tile: an operand is staged once for nine (four) products instead of
+// once per column block of (tap, channel).  Both operands lie in LDS as they
+// lie in memory, [pixel][32 channels]; ds_read_b64_tr_b16 turns eight pixels of
+// a channel into an MFMA fragment, so nothing is transposed in registers and a
+// tap is only a shift of the pixel index.  The eight waves of a block take
+// 16 pixels each of a 128-pixel stage and add their sums through LDS at the
+// end, in wave order.
+//   MODE 0, 3x3: the reduction runs over a padded pixel index in which every row
+//     has one zero pixel and every image one zero row after it, so a shifted
+//     pixel outside its image reads zeros.  (Where a padding pixel itself is one
+//     of a wave's 16, its lanes read a zero pixel for every tap: its dy is zero,
+//     but zero times an infinite x is not.)  x is held in a ring that covers the
+//     stage and one row and pixel on both sides; its first 16 pixels are
+//     repeated after its end, so a fragment never wraps.
+//   MODE 1, transposed 2x2: over the input pixels; dy is staged per tap.
+// Bound by LDS reads (ten fragments for nine products) and the matrix cores
+// alike; the staging's global loads run one stage ahead in registers.
+// ---------------------------------------------------------------------------
+constexpr int kWgThreads = 512;    // eight waves, 16 pixels of a stage each
+constexpr int kWgStage = 128;      // pixels per stage
+constexpr int kWgRow = 64;         // bytes of a staged pixel (32 channels)
+
+// Blocks of 128 ring pixels that a 3x3 stage needs ahead of its own, and the
+// widest image a ring of rs pixels holds (the ring also keeps the stage before
+// and takes the block being written).
+constexpr int wg_lead(int w) { return (2 * (w + 1) + 129) / kWgStage; }
+constexpr bool wg_ring_fits(int w, int rs) { return (wg_lead(w) + 2) * kWgStage <= rs; }
+
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef short short8v __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) short4v lds_short4;
+
+// MFMA fragment of 16 consecutive staged pixels (byte address of the first)
+// by 32 channels.  Within 16 lanes, lane i receives element i % 4 of the
+// 8-byte words that lanes i / 4, 4 + i / 4, 8 + i / 4, 12 + i / 4 address; so lane l
+// addresses pixel 8 (l / 32) + (l % 16) / 4, channels 16 (l / 16 % 2) + 4 (l % 4),
+// and the same four pixels further on.
+__device__ __forceinline__ int tr_lane_offset(int lane) {
+  return (8 * (lane >> 5) + ((lane & 15) >> 2)) * kWgRow + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
+}
+__device__ __forceinline__ bf16x8 tr_fragment(lds_char *first, lds_char *second) {
+  const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)first);
+  const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)second);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ bf16x8 tr_fragment(lds_char *p) { return tr_fragment(p, p + 4 * kWgRow); }
+
+// A pixel index split into (image, row, column) of an image grid of rows x cols
+// slots, advanced by one stage at a time.
+struct PixelWalk {
+  int img, row, col;
+  __device__ __forceinline__ void start(int64_t q, int rows, int cols) {  // q >= -rows * cols
+    const int64_t area = (int64_t)rows * cols;
+    const int64_t s = q + area;
+    img = (int)(s / area) - 1;
+    const int rem = (int)(s - (img + 1) * area);
+    row = rem / cols;
+    col = rem - row * cols;
+  }
+  __device__ __forceinline__ void next(int rows, int cols) {
+    const int dr = kWgStage / cols, di = dr / rows;
+    col += kWgStage - dr * cols;
+    int r = dr - di * rows;
+    if (col >= cols) { col -= cols; ++r; }
+    row += r;
+    img += di;
+    if (row >= rows) { row -= rows; ++img; }  // row + r is at most 2 rows - 1
+  }
+};
+
+template <int MODE, int RS>
+__global__ __launch_bounds__(kWgThreads) void wgrad_taps(WgradArgs a, int kb, int64_t chunk, int ci_tiles,
+                                                         int tiles) {
+  constexpr int NT = MODE == 0 ? 9 : 4;      // taps
+  constexpr int NA = MODE == 0 ? 1 : 4;      // dy tiles per stage
+  // x: the ring, its first 16 pixels again and a zero pixel; or two stages
+  constexpr int kX = MODE == 0 ? (RS + 17) * kWgRow : 2 * kWgStage * kWgRow;
+  constexpr int kDy = kWgStage * kWgRow;     // one dy tile
+  constexpr int kRed = 8 * 1024 * 4;         // eight waves' sums of one tap
+  constexpr int kBytes = kX + 2 * NA * kDy > kRed ? kX + 2 * NA * kDy : kRed;
+  __shared__ __attribute__((aligned(16))) char smem[kBytes];
+  char *const sx = smem, *const sdy = smem + kX;
+  lds_char *const lx = (lds_char *)sx, *const ldy = (lds_char *)sdy;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // blocks of one chunk read the same pixels: on one XCD where chunks come in eights
+  const int bid = blockIdx.x;
+  const bool by8 = (kb & 7) == 0;
+  const int ck = by8 ? (bid / (8 * tiles)) * 8 + (bid & 7) : bid % kb;
+  const int tile = by8 ? (bid >> 3) % tiles : bid / kb;
+  const int m0 = (tile / ci_tiles) * 32, n0 = (tile % ci_tiles) * 32;
+  const bool bias = a.bpartial && n0 == 0;
+  const int cols = MODE == 0 ? a.w + 1 : a.w, rows = MODE == 0 ? a.h + 1 : a.h;
+  const int64_t total = (int64_t)a.n * rows * cols;
+  const int64_t k0 = ck * chunk;
+  const int64_t k1 = k0 + chunk < total ? k0 + chunk : total;
+  const int stages = k1 > k0 ? (int)((k1 - k0 + kWgStage - 1) / kWgStage) : 0;
+  // this thread stages one 16-byte piece (8 channels) of pixel px of every 128
+  const int px = tid >> 2, ch = 8 * (tid & 3);
+  const bool xc = n0 + ch < a.cin, dc = m0 + ch < a.cout;
+  const uint16_t *const xg = a.x + a.x_co + n0 + ch;
+  const uint16_t *const dg = a.dy + a.dy_co + m0 + ch;
+  PixelWalk wx, wd;
+  auto load_x = [&]() -> uint4 {
+    const bool in = xc && wx.img >= 0 && wx.img < a.n && wx.row < a.h && wx.col < a.w;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (in) v = *reinterpret_cast<const uint4 *>(xg + (((int64_t)wx.img * a.h + wx.row) * a.w + wx.col) * a.x_cs);
+    return v;
+  };
+  uint4 rdy[NA], rx = make_uint4(0, 0, 0, 0);
+  unsigned long long pad = 0;  // bits 4 j: pixel j of this wave's 16 is padding
+  auto load_dy = [&]() {
+    const bool real = wd.img < a.n && wd.row < a.h && wd.col < a.w, in = dc && real;
+    pad = __ballot(!real);
+#pragma unroll
+    for (int t = 0; t < NA; ++t) {
+      int64_t p;
+      if constexpr (MODE == 0) p = ((int64_t)wd.img * a.h + wd.row) * a.w + wd.col;
+      else p = ((int64_t)wd.img * 2 * a.h + 2 * wd.row + (t >> 1)) * 2 * a.w + 2 * wd.col + (t & 1);
+      rdy[t] = make_uint4(0, 0, 0, 0);
+      if (in) rdy[t] = *reinterpret_cast<const uint4 *>(dg + p * a.dy_cs);
+    }
+  };
+  const int lead = MODE == 0 ? wg_lead(a.w) : 0;
+  const int ring = MODE == 0 ? (lead + 2) * kWgStage : 2 * kWgStage;
+  int xw = 0;  // ring slot of the next block of 128 pixels to write
+  auto store_x = [&](const uint4 &v) {
+    const int slot = xw + px;
+    *reinterpret_cast<uint4 *>(sx + slot * kWgRow + 2 * ch) = v;
+    if (MODE == 0 && slot < 16) *reinterpret_cast<uint4 *>(sx + (ring + slot) * kWgRow + 2 * ch) = v;
+    xw = xw + kWgStage == ring ? 0 : xw + kWgStage;
+  };
+  floatx16 acc[NT], bacc[NA];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = floatx16{};
+#pragma unroll
+  for (int t = 0; t < NA; ++t) bacc[t] = floatx16{};
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+  const int lo = tr_lane_offset(lane);
+  const int j0 = 8 * (lane >> 5) + ((lane & 15) >> 2);  // this lane's first fragment pixel
+  lds_char *const lzero = lx + (RS + 16) * kWgRow;
+  if (MODE == 0 && tid < 4) *reinterpret_cast<uint4 *>(sx + (RS + 16) * kWgRow + 16 * tid) = make_uint4(0, 0, 0, 0);
+  if (stages > 0) {
+    wd.start(k0 + px, rows, cols);
+    wx.start(MODE == 0 ? k0 - (cols + 1) + px : k0 + px, rows, cols);
+    for (int j = 0; j < lead; ++j) {
+      store_x(load_x());
+      wx.next(rows, cols);
+    }
+    load_dy();
+    rx = load_x();
+  }
+  int xr = 0;  // ring slot of the stage's first pixel less one row and one pixel
+  for (int i = 0; i < stages; ++i) {
+    char *const db = sdy + (i & 1) * NA * kDy;
+#pragma unroll
+    for (int t = 0; t < NA; ++t) *reinterpret_cast<uint4 *>(db + t * kDy + px * kWgRow + 2 * ch) = rdy[t];
+    store_x(rx);
+    const unsigned long long pads = pad;
+    __syncthreads();
+    if (i + 1 < stages) {
+      wd.next(rows, cols);
+      wx.next(rows, cols);
+      load_dy();
+      rx = load_x();
+    }
+    lds_char *const da = ldy + (i & 1) * NA * kDy + 16 * kWgRow * wave + lo;
+    bf16x8 A[NA];
+#pragma unroll
+    for (int t = 0; t < NA; ++t) A[t] = tr_fragment(da + t * kDy);
+    if constexpr (MODE == 0) {
+      auto first_pixel = [&](int t) {  // of tap t's 16, in the ring
+        const int slot = xr + 16 * wave + (t / 3) * cols + t % 3;
+        return lx + (slot >= ring ? slot - ring : slot) * kWgRow + lo;
+      };
+      const bool p0 = (pads >> (4 * j0)) & 1, p1 = (pads >> (4 * j0 + 16)) & 1;
+      auto fragment = [&](int t) {
+        lds_char *const p = first_pixel(t);
+        return tr_fragment(p0 ? lzero : p, p1 ? lzero : p + 4 * kWgRow);
+      };
+      // fragments two taps ahead of their product
+      bf16x8 B[3] = {fragment(0), fragment(1), {}};
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (t + 2 < NT) B[(t + 2) % 3] = fragment(t + 2);
+        acc[t] = mfma(A[0], B[t % 3], acc[t]);
+      }
+    } else {
+      const bf16x8 B = tr_fragment(lx + (xr + 16 * wave) * kWgRow + lo);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = mfma(A[t], B, acc[t]);
+    }
+    if (bias) {
+#pragma unroll
+      for (int t = 0; t < NA; ++t) bacc[t] = mfma(A[t], ones, bacc[t]);
+    }
+    xr = xr + kWgStage == ring ? 0 : xr + kWgStage;
+  }
+  // sums of the eight waves, tap by tap
+  float *const red = reinterpret_cast<float *>(smem);
+  const int ntap = MODE == 1 ? 4 : 1;
+  float *const out = a.partial + (int64_t)ck * ntap * a.cout * a.ncol;
+  auto sum_waves = [&](const floatx16 &v, float (&r)[2]) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) red[wave * 1024 + c_row(q, lane) * 32 + (lane & 31)] = v[q];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      r[k] = red[tid + 512 * k];
+#pragma unroll
+      for (int u = 1; u < 8; ++u) r[k] += red[u * 1024 + tid + 512 * k];
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    float r[2];
+    sum_waves(acc[t], r);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int m = m0 + (tid >> 5) + 16 * k, n = n0 + (tid & 31);
+      if (m >= a.cout || n >= a.cin) continue;
+      if constexpr (MODE == 0) out[(int64_t)m * a.ncol + t * a.cin + n] = r[k];
+      else out[((int64_t)t * a.cout + m) * a.ncol + n] = r[k];
+    }
+  }
+  if (bias) {  // uniform over the block
+#pragma unroll
+    for (int t = 0; t < NA; ++t) {
+      float r[2];
+      sum_waves(bacc[t], r);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int m = m0 + (tid >> 5) + 16 * k;
+        if ((tid & 31) == 0 && m < a.cout) a.bpartial[((int64_t)ck * ntap + t) * a.cout + m] = r[k];
+      }
+    }
+  }
+}
+
+// Launch the all-taps weight gradient; false where it does not apply (a 3x3
+// image too wide for the largest ring: 894 columns).
+template <int MODE>
+static bool launch_wgrad_taps(const WgradArgs &a, int kb, hipStream_t s) {
+  const int64_t total = MODE == 0 ? (int64_t)a.n * (a.h + 1) * (a.w + 1) : (int64_t)a.n * a.h * a.w;
+  const int64_t chunk = ((total + kb - 1) / kb + kWgStage - 1) / kWgStage * kWgStage;
+  const int ci_tiles = (a.cin + 31) / 32, tiles = ci_tiles * ((a.cout + 31) / 32);
+  if ((int64_t)kb * tiles > 0x7fffffff) return false;
+  const dim3 g((unsigned)((int64_t)kb * tiles));
+  if constexpr (MODE == 1) {
+    wgrad_taps<1, 0><<<g, kWgThreads, 0, s>>>(a, kb, chunk, ci_tiles, tiles);
+  } else {
+    if (wg_ring_fits(a.w, 640)) wgrad_taps<0, 640><<<g, kWgThreads, 0, s>>>(a, kb, chunk, ci_tiles, tiles);
+    else if (wg_ring_fits(a.w, 1024)) wgrad_taps<0, 1024><<<g, kWgThreads, 0, s>>>(a, kb, chunk, ci_tiles, tiles);
+    else if (wg_ring_fits(a.w, 2048)) wgrad_taps<0, 2048><<<g, kWgThreads, 0, s>>>(a, kb, chunk, ci_tiles, tiles);
+    else return false;
+  }
+  return true;
+}
+
 // sum_{k < count} p[k * stride] in a fixed order: eight interleaved partial
 // sums (k mod 8) combined pairwise, so the loads of a thread overlap.
 __device__ __forceinline__ float strided_sum(const float *p, int64_t count, int64_t stride) {
@@ -897,7 +1161,8 @@ int unet_conv3x3_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs
   const int kb = (int)((P + kWgradPix - 1) / kWgradPix);
   const int64_t wpart = (int64_t)kb * cout * 9 * cin;
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, 9 * cin, db ? partial + wpart : nullptr};
-  if (cout <= 32) {
+  if (launch_wgrad_taps<0>(a, kb, (hipStream_t)s)) {
+  } else if (cout <= 32) {
     dim3 g((unsigned)kb, 1, (unsigned)((9 * cin + 127) / 128));
     igemm_wgrad<0, 1, 4><<<g, 256, 0, (hipStream_t)s>>>(a);
   } else {
@@ -985,7 +1250,8 @@ int unet_upconv_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs,
   const int kb = (int)((P + kWgradPix - 1) / kWgradPix);
   const int64_t wpart = (int64_t)kb * 4 * cout * cin;
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, cin, db ? partial + wpart : nullptr};
-  if (cout <= 32) {
+  if (launch_wgrad_taps<1>(a, kb, (hipStream_t)s)) {
+  } else if (cout <= 32) {
     dim3 g((unsigned)kb, 1, (unsigned)(4 * ((cin + 127) / 128)));
     igemm_wgrad<1, 1, 4><<<g, 256, 0, (hipStream_t)s>>>(a);
   } else {
