@@ -348,21 +348,14 @@ static void launch_igemm(const GemmArgs &a, int64_t P, int taps_z, hipStream_t s
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradients (split over pixels): partial[kb][m][n] = sum over this
-// block's pixel chunk of A(m, p) B(p, n).
+// Weight gradients (split over pixels): partial[kb][tap][m][n] = sum over the
+// kb-th share of the pixels of A(m, p) B(p, n).
 //   MODE 0, 3x3: m = co, n = (tap, ci): A = dy[p][co], B = x[p + off(tap)][ci]
-//   MODE 1, transposed 2x2, tap = blockIdx.z: m = co, n = ci:
+//   MODE 1, transposed 2x2: m = co, n = ci:
 //          A = dy[2p + tap][co], B = x[p][ci]  (p over the input grid)
-// Per stage of 128 pixels, each thread loads an 8-pixel x 8-channel block of
-// one operand (eight 16-byte vectors), transposes it in registers (byte
-// permutes) and writes it channel-major to LDS as eight 16-byte vectors, so
-// an MFMA operand fragment (8 consecutive pixels of one channel) is one
-// 128-bit LDS read and neither side of LDS sees bank conflicts.  Channel
-// counts, strides and offsets are multiples of 8.
+// Channel counts, strides and offsets are multiples of 8.
 // ---------------------------------------------------------------------------
-constexpr int kWgradPix = 4096;  // pixels per block (split-K chunk)
-constexpr int kStagePix = 128;   // pixels per LDS stage
-constexpr int kStageLd = kStagePix + 8;
+constexpr int kWgradPix = 4096;  // pixels per partial sum
 
 struct WgradArgs {
   const uint16_t *x;
@@ -374,351 +367,226 @@ struct WgradArgs {
   float *bpartial;                // [kblocks][ntap][cout] bias partial sums, or NULL
 };
 
-// 8 x 8 transpose of 16-bit values: in[p] holds channels 0..7 of pixel p,
-// out[c] receives pixels 0..7 of channel c.
-__device__ __forceinline__ void transpose8x8(const uint4 (&in)[8], uint4 (&out)[8]) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    uint32_t lo[4], hi[4];  // channel 2j and 2j + 1, pixel pairs i
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t a = (&in[2 * i].x)[j], b = (&in[2 * i + 1].x)[j];
-      lo[i] = __builtin_amdgcn_perm(b, a, 0x05040100u);
-      hi[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-    }
-    out[2 * j] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-    out[2 * j + 1] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-  }
-}
-
-// Block tile (32 MT) x (32 NT) of C with MT * NT = 4 waves, each one 32 x 32
-// MFMA tile: (2, 2) in general, (1, 4) when the output channels fit 32.
-template <int MODE, int MT, int NT>
-__global__ __launch_bounds__(256) void igemm_wgrad(WgradArgs a) {
-  static_assert(MT * NT == 4, "four waves");
-  __shared__ __attribute__((aligned(16))) uint16_t sA[32 * MT][kStageLd];  // [m][pixel]
-  __shared__ __attribute__((aligned(16))) uint16_t sB[32 * NT][kStageLd];  // [n][pixel]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % MT, wn = wave / MT;
-  const int half = lane >> 5;
-  const int64_t P = (int64_t)a.n * a.h * a.w;
-  const int64_t p_begin = (int64_t)blockIdx.x * kWgradPix;
-  const int m0 = blockIdx.y * 32 * MT;  // output channel block
-  const int tapz = MODE == 1 ? (int)(blockIdx.z % 4) : 0;
-  const int nblk = MODE == 1 ? (int)(blockIdx.z / 4) : (int)blockIdx.z;
-  const int n0 = nblk * 32 * NT;        // column block
-  floatx16 acc = {};
-  // the blocks of the first column block also sum dy over their pixels (bias)
-  const bool bias_blk = a.bpartial && nblk == 0 && tid < 32 * MT;
-  float bacc = 0.f;
-  const int64_t p_end = p_begin + kWgradPix < P ? p_begin + kWgradPix : P;
-  // staging: 8-pixel x 8-channel blocks, 64 MT of A then 64 NT of B; a
-  // thread owns entries tid and tid + 256.  The next stage's loads go to
-  // registers before this stage's products run; the transpose and the LDS
-  // stores follow the barrier that ends them.
-  constexpr int kEntries = 64 * (MT + NT), NE = (kEntries + 255) / 256;
-  uint4 v[NE][8];
-  auto load_stage = [&](int64_t pcs) {
-#pragma unroll
-    for (int j = 0; j < NE; ++j) {
-      const int e = tid + 256 * j;
-      const bool stage_b = e >= 64 * MT;
-      const int eo = stage_b ? e - 64 * MT : e;
-      const int cg = eo >> 4, pb = eo & 15;
-      // image, row and column of the first of the 8 consecutive pixels; the
-      // others follow by increments (wrapping at row and image ends)
-      const int64_t pfirst = pcs + pb * 8;
-      int pn = (int)(pfirst / ((int64_t)a.h * a.w));
-      const int rr0 = (int)(pfirst - (int64_t)pn * a.h * a.w);
-      int py = rr0 / a.w, px = rr0 - py * a.w;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int64_t p = pfirst + r;
-        if (r > 0 && ++px == a.w) {
-          px = 0;
-          if (++py == a.h) {
-            py = 0;
-            ++pn;
-          }
-        }
-        v[j][r] = make_uint4(0, 0, 0, 0);
-        if (e >= kEntries || p >= p_end) continue;
-        if (!stage_b) {
-          const int m = m0 + cg * 8;
-          if (m < a.cout) {
-            int64_t q;
-            if constexpr (MODE == 0) {
-              q = p;
-            } else {
-              const int H2 = 2 * a.h, W2 = 2 * a.w;
-              q = (int64_t)pn * H2 * W2 + (int64_t)(2 * py + (tapz >> 1)) * W2 + 2 * px + (tapz & 1);
-            }
-            v[j][r] = *reinterpret_cast<const uint4 *>(a.dy + q * a.dy_cs + a.dy_co + m);
-          }
-        } else {
-          const int nn = n0 + cg * 8;
-          if (nn < a.ncol) {
-            if constexpr (MODE == 0) {
-              const int tap = nn / a.cin, ci = nn - tap * a.cin;
-              const int yy = py + tap / 3 - 1, xx = px + tap % 3 - 1;
-              if (yy >= 0 && yy < a.h && xx >= 0 && xx < a.w)
-                v[j][r] = *reinterpret_cast<const uint4 *>(
-                    a.x + ((int64_t)pn * a.h * a.w + (int64_t)yy * a.w + xx) * a.x_cs + a.x_co + ci);
-            } else {
-              v[j][r] = *reinterpret_cast<const uint4 *>(a.x + p * a.x_cs + a.x_co + nn);
-            }
-          }
-        }
-      }
-    }
-  };
-  if (p_begin < p_end) load_stage(p_begin);
-  for (int64_t pc = p_begin; pc < p_end; pc += kStagePix) {
-#pragma unroll
-    for (int j = 0; j < NE; ++j) {
-      const int e = tid + 256 * j;
-      if (e >= kEntries) continue;
-      const bool stage_b = e >= 64 * MT;
-      const int eo = stage_b ? e - 64 * MT : e;
-      const int cg = eo >> 4, pb = eo & 15;
-      uint4 t[8];
-      transpose8x8(v[j], t);
-      uint16_t(*dst)[kStageLd] = stage_b ? sB : sA;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) *reinterpret_cast<uint4 *>(&dst[cg * 8 + c][pb * 8]) = t[c];
-    }
-    __syncthreads();
-    if (pc + kStagePix < p_end) load_stage(pc + kStagePix);
-    if (bias_blk) {
-#pragma unroll
-      for (int q = 0; q < kStagePix; q += 8) {
-        const uint4 u = *reinterpret_cast<const uint4 *>(&sA[tid][q]);
-        const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) bacc += bf2f((uint16_t)(w4[k] & 0xffffu)) + bf2f((uint16_t)(w4[k] >> 16));
-      }
-    }
-#pragma unroll
-    for (int ks = 0; ks < kStagePix; ks += 16) {
-      const uint4 av = *reinterpret_cast<const uint4 *>(&sA[wm * 32 + (lane & 31)][ks + 8 * half]);
-      const uint4 bv = *reinterpret_cast<const uint4 *>(&sB[wn * 32 + (lane & 31)][ks + 8 * half]);
-      acc = mfma(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), acc);
-    }
-    __syncthreads();
-  }
-  const int ntap = MODE == 1 ? 4 : 1;
-  if (bias_blk && m0 + tid < a.cout)
-    a.bpartial[((int64_t)blockIdx.x * ntap + tapz) * a.cout + m0 + tid] = bacc;
-  const int nn = n0 + wn * 32 + (lane & 31);
-  if (nn >= a.ncol) return;
-  float *out = a.partial + ((int64_t)blockIdx.x * ntap + tapz) * (int64_t)a.cout * a.ncol;
-  for (int r = 0; r < 16; ++r) {
-    const int m = m0 + wm * 32 + c_row(r, lane);
-    if (m < a.cout) out[(int64_t)m * a.ncol + nn] = acc[r];
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Weight gradients with all taps in one block.  A block owns a chunk of pixels
-// and a 32 x 32 tile of (output, input) channels and accumulates every tap of
-// that tile: an operand is staged once for nine (four) products instead of
-// once per column block of (tap, channel).  Both operands lie in LDS as they
-// lie in memory, [pixel][32 channels]; ds_read_b64_tr_b16 turns eight pixels of
-// a channel into an MFMA fragment, so nothing is transposed in registers and a
-// tap is only a shift of the pixel index.  The eight waves of a block take
-// 16 pixels each of a 128-pixel stage and add their sums through LDS at the
-// end, in wave order.
-//   MODE 0, 3x3: the reduction runs over a padded pixel index in which every row
-//     has one zero pixel and every image one zero row after it, so a shifted
-//     pixel outside its image reads zeros.  (Where a padding pixel itself is one
-//     of a wave's 16, its lanes read a zero pixel for every tap: its dy is zero,
-//     but zero times an infinite x is not.)  x is held in a ring that covers the
-//     stage and one row and pixel on both sides; its first 16 pixels are
-//     repeated after its end, so a fragment never wraps.
-//   MODE 1, transposed 2x2: over the input pixels; dy is staged per tap.
-// Bound by LDS reads (ten fragments for nine products) and the matrix cores
-// alike; the staging's global loads run one stage ahead in registers.
+// Weight gradients with all taps in one wave.  A wave owns a 32 x 32 tile of
+// (output, input) channels and marches down image rows, 16 pixels of a row
+// at a time, accumulating every tap of that tile: a row of x enters three
+// products per column shift (with the dy rows above, at and below it), so its
+// fragments stay in registers for three steps and an LDS read feeds more than
+// one product.  Both operands pass through LDS as they lie in memory, [pixel][32
+// channels], in a piece of LDS of the wave's own (no barrier in the loop):
+// ds_read_b64_tr_b16 turns eight pixels of a channel into an MFMA fragment, and
+// a column shift is an offset of one pixel.  Global loads run kDepth rows ahead.
+//   MODE 0, 3x3: steps run over 16-column segments, images and rows, with one
+//     zero row after every image (it supplies the zero row above and below;
+//     its own products are skipped).
+//   MODE 1, transposed 2x2: a step is 16 input pixels and their four dy pixels.
+// The eight waves of a block take consecutive step ranges and add their sums
+// through LDS at the end, in wave order; a block writes one partial sum.
 // ---------------------------------------------------------------------------
-constexpr int kWgThreads = 512;    // eight waves, 16 pixels of a stage each
-constexpr int kWgStage = 128;      // pixels per stage
-constexpr int kWgRow = 64;         // bytes of a staged pixel (32 channels)
-
-// Blocks of 128 ring pixels that a 3x3 stage needs ahead of its own, and the
-// widest image a ring of rs pixels holds (the ring also keeps the stage before
-// and takes the block being written).
-constexpr int wg_lead(int w) { return (2 * (w + 1) + 129) / kWgStage; }
-constexpr bool wg_ring_fits(int w, int rs) { return (wg_lead(w) + 2) * kWgStage <= rs; }
+constexpr int kWgThreads = 512;  // eight waves
+constexpr int kPixBytes = 64;    // a staged pixel: 32 channels
 
 typedef short short4v __attribute__((ext_vector_type(4)));
-typedef short short8v __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) short4v lds_short4;
 
-// MFMA fragment of 16 consecutive staged pixels (byte address of the first)
-// by 32 channels.  Within 16 lanes, lane i receives element i % 4 of the
-// 8-byte words that lanes i / 4, 4 + i / 4, 8 + i / 4, 12 + i / 4 address; so lane l
-// addresses pixel 8 (l / 32) + (l % 16) / 4, channels 16 (l / 16 % 2) + 4 (l % 4),
-// and the same four pixels further on.
-__device__ __forceinline__ int tr_lane_offset(int lane) {
-  return (8 * (lane >> 5) + ((lane & 15) >> 2)) * kWgRow + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-}
+// MFMA fragment of 16 consecutive staged pixels by 32 channels from two reads.
+// Within 16 lanes, lane i receives element i % 4 of the 8-byte words that lanes
+// i / 4, 4 + i / 4, 8 + i / 4 and 12 + i / 4 address; so lane l addresses pixel
+// 8 (l / 32) + (l % 16) / 4, channels 16 (l / 16 % 2) + 4 (l % 4), first, and the
+// same four pixels further on, second.
+__device__ __forceinline__ int tr_pixel(int lane) { return 8 * (lane >> 5) + ((lane & 15) >> 2); }
+__device__ __forceinline__ int tr_channel_bytes(int lane) { return (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2; }
 __device__ __forceinline__ bf16x8 tr_fragment(lds_char *first, lds_char *second) {
   const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)first);
   const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)second);
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
-__device__ __forceinline__ bf16x8 tr_fragment(lds_char *p) { return tr_fragment(p, p + 4 * kWgRow); }
 
-// A pixel index split into (image, row, column) of an image grid of rows x cols
-// slots, advanced by one stage at a time.
-struct PixelWalk {
-  int img, row, col;
-  __device__ __forceinline__ void start(int64_t q, int rows, int cols) {  // q >= -rows * cols
-    const int64_t area = (int64_t)rows * cols;
-    const int64_t s = q + area;
-    img = (int)(s / area) - 1;
-    const int rem = (int)(s - (img + 1) * area);
-    row = rem / cols;
-    col = rem - row * cols;
-  }
-  __device__ __forceinline__ void next(int rows, int cols) {
-    const int dr = kWgStage / cols, di = dr / rows;
-    col += kWgStage - dr * cols;
-    int r = dr - di * rows;
-    if (col >= cols) { col -= cols; ++r; }
-    row += r;
-    img += di;
-    if (row >= rows) { row -= rows; ++img; }  // row + r is at most 2 rows - 1
-  }
-};
+// Buffer loads: a wave-uniform base, a byte offset per lane, and zeros from
+// offsets beyond the buffer.  Loads masked this way are issued by every lane on
+// every path, so the compiler can wait for the oldest of several in flight.
+typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
+constexpr uint32_t kOutside = 0xffffffffu;       // offset of a masked lane
+constexpr uint32_t kWholeBuffer = 0xfffffff0u;  // bytes reachable from a base
+__device__ __forceinline__ uint4 buffer_load16(const uint16_t *base, uint32_t bytes, uint32_t offset) {
+  auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, (int)bytes, 0x00027000);
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)offset, 0, 0));
+}
 
-template <int MODE, int RS>
-__global__ __launch_bounds__(kWgThreads) void wgrad_taps(WgradArgs a, int kb, int64_t chunk, int ci_tiles,
+// Steps of a weight gradient: segments of 16 columns by (image, row) slots.
+template <int MODE> __host__ __device__ inline int64_t wg_rows(const WgradArgs &a) {
+  return (int64_t)a.n * (MODE == 0 ? a.h + 1 : a.h);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(kWgThreads) void wgrad_taps(WgradArgs a, int kb, int64_t steps_per_wave, int ci_tiles,
                                                          int tiles) {
-  constexpr int NT = MODE == 0 ? 9 : 4;      // taps
-  constexpr int NA = MODE == 0 ? 1 : 4;      // dy tiles per stage
-  // x: the ring, its first 16 pixels again and a zero pixel; or two stages
-  constexpr int kX = MODE == 0 ? (RS + 17) * kWgRow : 2 * kWgStage * kWgRow;
-  constexpr int kDy = kWgStage * kWgRow;     // one dy tile
-  constexpr int kRed = 8 * 1024 * 4;         // eight waves' sums of one tap
-  constexpr int kBytes = kX + 2 * NA * kDy > kRed ? kX + 2 * NA * kDy : kRed;
+  constexpr int NT = MODE == 0 ? 9 : 4;  // taps
+  constexpr int NA = MODE == 0 ? 1 : 4;  // dy tiles per step
+  constexpr int kDepth = 2;              // steps whose loads are in flight
+  constexpr int kXPix = MODE == 0 ? 18 : 16;
+  // a wave's LDS: x, three zero pixels, dy
+  constexpr int kZero = kXPix * kPixBytes, kDy = kZero + 3 * kPixBytes;
+  constexpr int kWave = kDy + NA * 16 * kPixBytes;
+  constexpr int kRed = 8 * 1024 * 4;  // eight waves' sums of one tap
+  constexpr int kBytes = 8 * kWave > kRed ? 8 * kWave : kRed;
   __shared__ __attribute__((aligned(16))) char smem[kBytes];
-  char *const sx = smem, *const sdy = smem + kX;
-  lds_char *const lx = (lds_char *)sx, *const ldy = (lds_char *)sdy;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // blocks of one chunk read the same pixels: on one XCD where chunks come in eights
+  char *const sw = smem + wave * kWave;
+  lds_char *const lw = (lds_char *)sw;
+  // blocks of one partial sum read the same pixels: on one XCD where they come in eights
   const int bid = blockIdx.x;
   const bool by8 = (kb & 7) == 0;
   const int ck = by8 ? (bid / (8 * tiles)) * 8 + (bid & 7) : bid % kb;
   const int tile = by8 ? (bid >> 3) % tiles : bid / kb;
   const int m0 = (tile / ci_tiles) * 32, n0 = (tile % ci_tiles) * 32;
   const bool bias = a.bpartial && n0 == 0;
-  const int cols = MODE == 0 ? a.w + 1 : a.w, rows = MODE == 0 ? a.h + 1 : a.h;
-  const int64_t total = (int64_t)a.n * rows * cols;
-  const int64_t k0 = ck * chunk;
-  const int64_t k1 = k0 + chunk < total ? k0 + chunk : total;
-  const int stages = k1 > k0 ? (int)((k1 - k0 + kWgStage - 1) / kWgStage) : 0;
-  // this thread stages one 16-byte piece (8 channels) of pixel px of every 128
-  const int px = tid >> 2, ch = 8 * (tid & 3);
+  const int rows = MODE == 0 ? a.h + 1 : a.h;
+  const int64_t rows_all = wg_rows<MODE>(a);
+  const int64_t total = rows_all * ((a.w + 15) / 16);
+  const int64_t u0 = ((int64_t)ck * 8 + wave) * steps_per_wave;
+  const int64_t u1 = u0 + steps_per_wave < total ? u0 + steps_per_wave : total;
+  // this lane stages channels ch .. ch + 7 of pixel px of the 16
+  const int px = lane >> 2, ch = 8 * (lane & 3);
   const bool xc = n0 + ch < a.cin, dc = m0 + ch < a.cout;
-  const uint16_t *const xg = a.x + a.x_co + n0 + ch;
-  const uint16_t *const dg = a.dy + a.dy_co + m0 + ch;
-  PixelWalk wx, wd;
-  auto load_x = [&]() -> uint4 {
-    const bool in = xc && wx.img >= 0 && wx.img < a.n && wx.row < a.h && wx.col < a.w;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (in) v = *reinterpret_cast<const uint4 *>(xg + (((int64_t)wx.img * a.h + wx.row) * a.w + wx.col) * a.x_cs);
-    return v;
+  const uint16_t *const xg = a.x + a.x_co + n0;
+  const uint16_t *const dg = a.dy + a.dy_co + m0;
+
+  // the step being loaded: segment, slot row within its image, real row over
+  // all images; it starts one step early in MODE 0 (the zero row before the
+  // first image where u0 = 0)
+  const int64_t first = MODE == 0 ? u0 - 1 : u0;
+  int seg, row;
+  int64_t lrow, slots_left;  // slots left in the segment
+  if (first < 0) {
+    seg = -1; row = rows - 1; lrow = 0; slots_left = 1;
+  } else {
+    seg = (int)(first / rows_all);
+    const int64_t r = first - seg * rows_all;
+    const int64_t img = r / rows;
+    row = (int)(r - img * rows);
+    lrow = img * a.h + row;
+    slots_left = rows_all - r;
+  }
+  // byte offsets of this lane's pieces from the segment's first pixel (x: one
+  // pixel before it in MODE 0)
+  uint32_t xoff, hoff, doff;
+  auto columns = [&]() {
+    const int c = 16 * seg + px - (MODE == 0 ? 1 : 0);
+    xoff = xc && c >= 0 && c < a.w ? 2u * (uint32_t)(px * a.x_cs + ch) : kOutside;
+    hoff = xc && lane < 8 && c + 16 < a.w ? 2u * (uint32_t)((px + 16) * a.x_cs + ch) : kOutside;
+    doff = dc && 16 * seg + px < a.w ? 2u * (uint32_t)((MODE == 0 ? px : 2 * px) * a.dy_cs + ch) : kOutside;
   };
-  uint4 rdy[NA], rx = make_uint4(0, 0, 0, 0);
-  unsigned long long pad = 0;  // bits 4 j: pixel j of this wave's 16 is padding
-  auto load_dy = [&]() {
-    const bool real = wd.img < a.n && wd.row < a.h && wd.col < a.w, in = dc && real;
-    pad = __ballot(!real);
+  columns();
+  struct Staged {  // this lane's pieces of one step, on their way to LDS
+    uint4 x, xh, dy[NA];
+    int seg;
+    bool real;
+  } st[kDepth];
+  int64_t u = first;
+  auto load = [&](Staged &g) __attribute__((always_inline)) {
+    const bool on = (MODE == 1 || row < a.h) && seg >= 0 && u <= u1;
+    const uint32_t bytes = on ? kWholeBuffer : 0;
+    g.real = on && u >= u0 && u < u1;
+    g.seg = seg;
+    const int64_t pix = lrow * a.w + 16 * seg;
+    const uint16_t *const xp = xg + (pix - (MODE == 0 ? 1 : 0)) * a.x_cs;
+    g.x = buffer_load16(xp, bytes, xoff);
+    if constexpr (MODE == 0) g.xh = buffer_load16(xp, bytes, hoff);
 #pragma unroll
     for (int t = 0; t < NA; ++t) {
-      int64_t p;
-      if constexpr (MODE == 0) p = ((int64_t)wd.img * a.h + wd.row) * a.w + wd.col;
-      else p = ((int64_t)wd.img * 2 * a.h + 2 * wd.row + (t >> 1)) * 2 * a.w + 2 * wd.col + (t & 1);
-      rdy[t] = make_uint4(0, 0, 0, 0);
-      if (in) rdy[t] = *reinterpret_cast<const uint4 *>(dg + p * a.dy_cs);
+      const int64_t dpix = MODE == 0 ? pix : (2 * lrow + (t >> 1)) * 2 * a.w + 32 * seg + (t & 1);
+      g.dy[t] = buffer_load16(dg + dpix * a.dy_cs, bytes, doff);
+    }
+    // on to the next step
+    ++u;
+    if (MODE == 1 || row < a.h) ++lrow;
+    if (++row == rows) row = 0;
+    if (--slots_left == 0) {
+      slots_left = rows_all;
+      lrow = 0;
+      ++seg;
+      columns();
     }
   };
-  const int lead = MODE == 0 ? wg_lead(a.w) : 0;
-  const int ring = MODE == 0 ? (lead + 2) * kWgStage : 2 * kWgStage;
-  int xw = 0;  // ring slot of the next block of 128 pixels to write
-  auto store_x = [&](const uint4 &v) {
-    const int slot = xw + px;
-    *reinterpret_cast<uint4 *>(sx + slot * kWgRow + 2 * ch) = v;
-    if (MODE == 0 && slot < 16) *reinterpret_cast<uint4 *>(sx + (ring + slot) * kWgRow + 2 * ch) = v;
-    xw = xw + kWgStage == ring ? 0 : xw + kWgStage;
-  };
-  floatx16 acc[NT], bacc[NA];
+  lds_char *p0 = lw, *p1 = lw;  // this lane's x fragment pixels
+  int pseg = -2;                // the segment they are set for
+  const int j0 = tr_pixel(lane), tc = tr_channel_bytes(lane);
+  floatx16 acc[NT];
+  float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // of this lane's dy channels
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = floatx16{};
+  bf16x8 A[2][NA], B[3][MODE == 0 ? 3 : 1];
+  bool real[2] = {false, false};
+  if (lane < 12) *reinterpret_cast<uint4 *>(sw + kZero + 16 * lane) = make_uint4(0, 0, 0, 0);
+  // an iteration brings in one step and runs the products of the one before it;
+  // a few more than needed run at the end, on zeros
+  const int iters = u0 < u1 ? (int)(u1 - first + 1) : 0;
+  if (iters > 0) {
 #pragma unroll
-  for (int t = 0; t < NA; ++t) bacc[t] = floatx16{};
-  const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
-  const int lo = tr_lane_offset(lane);
-  const int j0 = 8 * (lane >> 5) + ((lane & 15) >> 2);  // this lane's first fragment pixel
-  lds_char *const lzero = lx + (RS + 16) * kWgRow;
-  if (MODE == 0 && tid < 4) *reinterpret_cast<uint4 *>(sx + (RS + 16) * kWgRow + 16 * tid) = make_uint4(0, 0, 0, 0);
-  if (stages > 0) {
-    wd.start(k0 + px, rows, cols);
-    wx.start(MODE == 0 ? k0 - (cols + 1) + px : k0 + px, rows, cols);
-    for (int j = 0; j < lead; ++j) {
-      store_x(load_x());
-      wx.next(rows, cols);
-    }
-    load_dy();
-    rx = load_x();
+    for (int v = 0; v < kDepth; ++v) load(st[v]);
   }
-  int xr = 0;  // ring slot of the stage's first pixel less one row and one pixel
-  for (int i = 0; i < stages; ++i) {
-    char *const db = sdy + (i & 1) * NA * kDy;
+  auto iterate = [&](Staged &g, bf16x8 (&An)[NA], const bf16x8 (&Ac)[NA], bool &real_n, bool real_c,
+                     bf16x8 (&Bu)[MODE == 0 ? 3 : 1], const bf16x8 (&Bm)[MODE == 0 ? 3 : 1],
+                     bf16x8 (&Bd)[MODE == 0 ? 3 : 1]) __attribute__((always_inline)) {
+    // LDS operations of a wave are done in order: these writes follow the
+    // last step's reads
+    *reinterpret_cast<uint4 *>(sw + 16 * lane) = g.x;
+    if (MODE == 0 && lane < 8) *reinterpret_cast<uint4 *>(sw + 16 * kPixBytes + 16 * lane) = g.xh;
 #pragma unroll
-    for (int t = 0; t < NA; ++t) *reinterpret_cast<uint4 *>(db + t * kDy + px * kWgRow + 2 * ch) = rdy[t];
-    store_x(rx);
-    const unsigned long long pads = pad;
-    __syncthreads();
-    if (i + 1 < stages) {
-      wd.next(rows, cols);
-      wx.next(rows, cols);
-      load_dy();
-      rx = load_x();
+    for (int t = 0; t < NA; ++t) *reinterpret_cast<uint4 *>(sw + kDy + t * 16 * kPixBytes + 16 * lane) = g.dy[t];
+    if (g.seg != pseg) {
+      // columns outside the image read a zero pixel: their dy is zero, but zero
+      // times an infinite x is not
+      pseg = g.seg;
+      const bool o0 = 16 * pseg + j0 >= a.w, o1 = 16 * pseg + j0 + 4 >= a.w;
+      p0 = lw + (o0 ? kZero : j0 * kPixBytes + tc);
+      p1 = lw + (o1 ? kZero : (j0 + 4) * kPixBytes + tc);
     }
-    lds_char *const da = ldy + (i & 1) * NA * kDy + 16 * kWgRow * wave + lo;
-    bf16x8 A[NA];
+    real_n = g.real;
+    if (bias && g.real) {
 #pragma unroll
-    for (int t = 0; t < NA; ++t) A[t] = tr_fragment(da + t * kDy);
+      for (int t = 0; t < NA; ++t) {
+        const uint32_t d4[4] = {g.dy[t].x, g.dy[t].y, g.dy[t].z, g.dy[t].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          bsum[2 * k] += __uint_as_float(d4[k] << 16);
+          bsum[2 * k + 1] += __uint_as_float(d4[k] & 0xffff0000u);
+        }
+      }
+    }
+    load(g);
+#pragma unroll
+    for (int c = 0; c < (MODE == 0 ? 3 : 1); ++c) Bd[c] = tr_fragment(p0 + c * kPixBytes, p1 + c * kPixBytes);
+#pragma unroll
+    for (int t = 0; t < NA; ++t) {
+      lds_char *const q = lw + kDy + (t * 16 + j0) * kPixBytes + tc;
+      An[t] = tr_fragment(q, q + 4 * kPixBytes);
+    }
     if constexpr (MODE == 0) {
-      auto first_pixel = [&](int t) {  // of tap t's 16, in the ring
-        const int slot = xr + 16 * wave + (t / 3) * cols + t % 3;
-        return lx + (slot >= ring ? slot - ring : slot) * kWgRow + lo;
-      };
-      const bool p0 = (pads >> (4 * j0)) & 1, p1 = (pads >> (4 * j0 + 16)) & 1;
-      auto fragment = [&](int t) {
-        lds_char *const p = first_pixel(t);
-        return tr_fragment(p0 ? lzero : p, p1 ? lzero : p + 4 * kWgRow);
-      };
-      // fragments two taps ahead of their product
-      bf16x8 B[3] = {fragment(0), fragment(1), {}};
+      if (real_c) {  // rows above, at, below
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        if (t + 2 < NT) B[(t + 2) % 3] = fragment(t + 2);
-        acc[t] = mfma(A[0], B[t % 3], acc[t]);
+        for (int c = 0; c < 3; ++c) acc[c] = mfma(Ac[0], Bu[c], acc[c]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[3 + c] = mfma(Ac[0], Bm[c], acc[3 + c]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[6 + c] = mfma(Ac[0], Bd[c], acc[6 + c]);
       }
     } else {
-      const bf16x8 B = tr_fragment(lx + (xr + 16 * wave) * kWgRow + lo);
+      if (real_c) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = mfma(A[t], B, acc[t]);
+        for (int t = 0; t < 4; ++t) acc[t] = mfma(Ac[t], Bm[0], acc[t]);
+      }
     }
-    if (bias) {
+  };
+  for (int j = 0; j < iters; j += 6) {
 #pragma unroll
-      for (int t = 0; t < NA; ++t) bacc[t] = mfma(A[t], ones, bacc[t]);
-    }
-    xr = xr + kWgStage == ring ? 0 : xr + kWgStage;
+    for (int v = 0; v < 6; ++v)
+      iterate(st[v % kDepth], A[v & 1], A[(v + 1) & 1], real[v & 1], real[(v + 1) & 1], B[(v + 1) % 3],
+              B[(v + 2) % 3], B[v % 3]);
   }
   // sums of the eight waves, tap by tap
   float *const red = reinterpret_cast<float *>(smem);
@@ -748,38 +616,25 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_taps(WgradArgs a, int kb, in
       else out[((int64_t)t * a.cout + m) * a.ncol + n] = r[k];
     }
   }
-  if (bias) {  // uniform over the block
+  if (bias) {  // uniform over the block; the sum over the taps counts as tap 0's
+    __syncthreads();
 #pragma unroll
-    for (int t = 0; t < NA; ++t) {
-      float r[2];
-      sum_waves(bacc[t], r);
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int m = m0 + (tid >> 5) + 16 * k;
-        if ((tid & 31) == 0 && m < a.cout) a.bpartial[((int64_t)ck * ntap + t) * a.cout + m] = r[k];
-      }
+    for (int k = 0; k < 8; ++k) red[(8 * (lane & 3) + k) * 128 + 16 * wave + px] = bsum[k];
+    __syncthreads();
+    if (tid < 32 && m0 + tid < a.cout) {
+      float r = 0.f;
+      for (int k = 0; k < 128; ++k) r += red[tid * 128 + (k + tid) % 128];
+      for (int t = 0; t < ntap; ++t) a.bpartial[((int64_t)ck * ntap + t) * a.cout + m0 + tid] = t ? 0.f : r;
     }
   }
 }
 
-// Launch the all-taps weight gradient; false where it does not apply (a 3x3
-// image too wide for the largest ring: 894 columns).
 template <int MODE>
-static bool launch_wgrad_taps(const WgradArgs &a, int kb, hipStream_t s) {
-  const int64_t total = MODE == 0 ? (int64_t)a.n * (a.h + 1) * (a.w + 1) : (int64_t)a.n * a.h * a.w;
-  const int64_t chunk = ((total + kb - 1) / kb + kWgStage - 1) / kWgStage * kWgStage;
+static void launch_wgrad_taps(const WgradArgs &a, int kb, hipStream_t s) {
+  const int64_t total = wg_rows<MODE>(a) * ((a.w + 15) / 16);
+  const int64_t per_wave = (total + 8 * (int64_t)kb - 1) / (8 * (int64_t)kb);
   const int ci_tiles = (a.cin + 31) / 32, tiles = ci_tiles * ((a.cout + 31) / 32);
-  if ((int64_t)kb * tiles > 0x7fffffff) return false;
-  const dim3 g((unsigned)((int64_t)kb * tiles));
-  if constexpr (MODE == 1) {
-    wgrad_taps<1, 0><<<g, kWgThreads, 0, s>>>(a, kb, chunk, ci_tiles, tiles);
-  } else {
-    if (wg_ring_fits(a.w, 640)) wgrad_taps<0, 640><<<g, kWgThreads, 0, s>>>(a, kb, chunk, ci_tiles, tiles);
-    else if (wg_ring_fits(a.w, 1024)) wgrad_taps<0, 1024><<<g, kWgThreads, 0, s>>>(a, kb, chunk, ci_tiles, tiles);
-    else if (wg_ring_fits(a.w, 2048)) wgrad_taps<0, 2048><<<g, kWgThreads, 0, s>>>(a, kb, chunk, ci_tiles, tiles);
-    else return false;
-  }
-  return true;
+  wgrad_taps<MODE><<<dim3((unsigned)((int64_t)kb * tiles)), kWgThreads, 0, s>>>(a, kb, per_wave, ci_tiles, tiles);
 }
 
 // sum_{k < count} p[k * stride] in a fixed order: eight interleaved partial
@@ -1161,14 +1016,7 @@ int unet_conv3x3_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs
   const int kb = (int)((P + kWgradPix - 1) / kWgradPix);
   const int64_t wpart = (int64_t)kb * cout * 9 * cin;
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, 9 * cin, db ? partial + wpart : nullptr};
-  if (launch_wgrad_taps<0>(a, kb, (hipStream_t)s)) {
-  } else if (cout <= 32) {
-    dim3 g((unsigned)kb, 1, (unsigned)((9 * cin + 127) / 128));
-    igemm_wgrad<0, 1, 4><<<g, 256, 0, (hipStream_t)s>>>(a);
-  } else {
-    dim3 g((unsigned)kb, (unsigned)((cout + 63) / 64), (unsigned)((9 * cin + 63) / 64));
-    igemm_wgrad<0, 2, 2><<<g, 256, 0, (hipStream_t)s>>>(a);
-  }
+  launch_wgrad_taps<0>(a, kb, (hipStream_t)s);
   wgrad_reduce<<<grid1d((int64_t)cout * 9 * cin), 256, 0, (hipStream_t)s>>>(partial, kb, 1, cout, 9 * cin, dw,
                                                                              accumulate);
   if (db) bias_reduce<<<(cout + 63) / 64, 64, 0, (hipStream_t)s>>>(partial + wpart, kb, cout, db, accumulate);
@@ -1250,14 +1098,7 @@ int unet_upconv_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs,
   const int kb = (int)((P + kWgradPix - 1) / kWgradPix);
   const int64_t wpart = (int64_t)kb * 4 * cout * cin;
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, cin, db ? partial + wpart : nullptr};
-  if (launch_wgrad_taps<1>(a, kb, (hipStream_t)s)) {
-  } else if (cout <= 32) {
-    dim3 g((unsigned)kb, 1, (unsigned)(4 * ((cin + 127) / 128)));
-    igemm_wgrad<1, 1, 4><<<g, 256, 0, (hipStream_t)s>>>(a);
-  } else {
-    dim3 g((unsigned)kb, (unsigned)((cout + 63) / 64), (unsigned)(4 * ((cin + 63) / 64)));
-    igemm_wgrad<1, 2, 2><<<g, 256, 0, (hipStream_t)s>>>(a);
-  }
+  launch_wgrad_taps<1>(a, kb, (hipStream_t)s);
   wgrad_reduce<<<grid1d((int64_t)4 * cout * cin), 256, 0, (hipStream_t)s>>>(partial, kb, 4, cout, cin, dw, 0);
   if (db) bias_reduce<<<(cout + 63) / 64, 64, 0, (hipStream_t)s>>>(partial + wpart, (int64_t)kb * 4, cout, db, 0);
   return launched();
