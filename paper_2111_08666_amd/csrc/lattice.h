@@ -354,10 +354,107 @@ __device__ __forceinline__ void collide_component(float (&fo)[Q], R rho, R ux, R
   fo[0] = (float)((R)fo[0] - moved);
 }
 
+// The same collision with the equilibrium and the source formed population by
+// population (SRT, TRT and D2Q9 MRT), for BF16-deviation storage: the two forms
+// differ in the last FP32 place, which there decides BF16 roundings, and a
+// state held in 8 bits departs by 1e-5 within a hundred steps.  States in
+// that storage go on as they were begun, bit for bit.
+template <int Q, int COLL, typename R>
+__device__ __forceinline__ void collide_by_population(float (&fo)[Q], R rho, R ux, R uy, R uz, R Fx,
+                                                  R Fy, R Fz, const Rates<R> &r) {
+  using L = Lat<Q>;
+  const R usq15 = R(1.5) * (ux * ux + uy * uy + uz * uz);
+  const R uF = ux * Fx + uy * Fy + uz * Fz;
+  R moved = 0;  // sum of the moving populations' changes
+  if constexpr (COLL == 0) {
+    const R om = r.s_nu, fac = R(1) - R(0.5) * om;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      R dv, S;
+      departure<Q, R>(i, fo[i], rho, ux, uy, uz, Fx, Fy, Fz, usq15, uF, dv, S);
+      const R df = om * dv + fac * S;
+      fo[i] = (float)((R)fo[i] + df);
+      moved += df;
+    }
+  } else if constexpr (COLL == 2) {
+    const R sp = r.s_nu, sm = r.s_q;
+    const R fp = R(1) - R(0.5) * sp, fm = R(1) - R(0.5) * sm;
+    // opposite pairs (i, b): the pair's symmetric and antisymmetric parts
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      const int b = L::opp[i];
+      if (b < i) continue;
+      // e_b = -e_i: the pair shares e.u and e.F up to sign, so the
+      // departures' halves come from one evaluation of each
+      const R eu = L::ex[i] * ux + L::ey[i] * uy + L::ez[i] * uz;
+      const R eF = L::ex[i] * Fx + L::ey[i] * Fy + L::ez[i] * Fz;
+      const R w = (R)L::w[i], wr = w * rho;
+      const R ai = fmar<R>(w, rho, -(R)fo[i]), ab = fmar<R>(w, rho, -(R)fo[b]);
+      const R dv_p = R(0.5) * (ai + ab) + wr * (R(4.5) * eu * eu - usq15);  // (dv_i + dv_b) / 2
+      const R dv_m = R(0.5) * (ai - ab) + wr * R(3) * eu;                    // (dv_i - dv_b) / 2
+      const R S_p = w * (R(9) * eu * eF - R(3) * uF), S_m = w * R(3) * eF;
+      const R dp = sp * dv_p + fp * S_p;  // change of the symmetric part
+      const R dm = sm * dv_m + fm * S_m;  // change of the antisymmetric part
+      fo[i] = (float)((R)fo[i] + (dp + dm));
+      fo[b] = (float)((R)fo[b] + (dp - dm));
+      moved += R(2) * dp;
+    }
+  } else {
+    // D2Q9 MRT: moments (Lallemand-Luo rows e, eps, jx, qx, jy, qy, pxx,
+    // pxy) of the departures from equilibrium and of the source
+    R d[Q], S[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) departure<Q, R>(i, fo[i], rho, ux, uy, uz, Fx, Fy, Fz, usq15, uF, d[i], S[i]);
+    auto mom = [](const R(&f)[Q], R(&m)[8]) {
+      const R a = f[1] + f[2] + f[3] + f[4];
+      const R dg = f[5] + f[6] + f[7] + f[8];
+      const R d13 = f[1] - f[3], d24 = f[2] - f[4];
+      const R p5 = f[5] - f[7], p6 = f[6] - f[8];
+      m[0] = R(-4) * f[0] - a + R(2) * dg;      // e
+      m[1] = R(4) * f[0] - R(2) * a + dg;       // eps
+      m[2] = d13 + p5 - p6;                     // jx
+      m[3] = R(-2) * d13 + p5 - p6;             // qx
+      m[4] = d24 + p5 + p6;                     // jy
+      m[5] = R(-2) * d24 + p5 + p6;             // qy
+      m[6] = (f[1] + f[3]) - (f[2] + f[4]);     // pxx
+      m[7] = (f[5] + f[7]) - (f[6] + f[8]);     // pxy
+    };
+    R md[8], ms[8];
+    mom(d, md);
+    mom(S, ms);
+    const R sr[8] = {r.s_e, r.s_eps, r.s_j, r.s_q, r.s_j, r.s_q, r.s_nu, r.s_nu};
+    R dmv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) dmv[k] = sr[k] * md[k] + (R(1) - R(0.5) * sr[k]) * ms[k];
+    // f += M^-1 dm, M^-1 = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4)
+    const R ce = dmv[0] * R(1.0 / 36.0), cp = dmv[1] * R(1.0 / 36.0);
+    const R jx = dmv[2] * R(1.0 / 6.0), qx = dmv[3] * R(1.0 / 12.0);
+    const R jy = dmv[4] * R(1.0 / 6.0), qy = dmv[5] * R(1.0 / 12.0);
+    const R pxx = dmv[6] * R(0.25), pxy = dmv[7] * R(0.25);
+    const R ax = -ce - R(2) * cp;
+    const R dd = R(2) * ce + cp;
+    const R df[Q] = {0,
+                     ax + jx - R(2) * qx + pxx,
+                     ax + jy - R(2) * qy - pxx,
+                     ax - jx + R(2) * qx + pxx,
+                     ax - jy + R(2) * qy - pxx,
+                     dd + jx + qx + jy + qy + pxy,
+                     dd - jx - qx + jy + qy - pxy,
+                     dd - jx - qx - jy - qy + pxy,
+                     dd + jx + qx - jy - qy - pxy};
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      fo[i] = (float)((R)fo[i] + df[i]);
+      moved += df[i];
+    }
+  }
+  fo[0] = (float)((R)fo[0] - moved);
+}
+
 // Mixture velocity, rates and the collision of both components at a node.
 // rho1/rho2 are the node densities, F the per-component forces
 // (interaction + body).
-template <int Q, int COLL, typename R>
+template <int Q, int COLL, int ST, typename R>
 __device__ __forceinline__ void collide_node(const InstDev &d, float (&f0)[Q], float (&f1)[Q], R rho1,
                                              R rho2, R F1x, R F1y, R F1z, R F2x, R F2y, R F2z) {
   using L = Lat<Q>;
@@ -380,8 +477,13 @@ __device__ __forceinline__ void collide_node(const InstDev &d, float (&f0)[Q], f
   const R uy = (jy + h * (F1y + F2y)) * inv_rho;
   const R uz = (jz + h * (F1z + F2z)) * inv_rho;
   const Rates<R> r = node_rates<R>(d, rho1, rho2, inv_rho);
-  collide_component<Q, COLL, R>(f0, rho1, ux, uy, uz, F1x, F1y, F1z, r);
-  collide_component<Q, COLL, R>(f1, rho2, ux, uy, uz, F2x, F2y, F2z, r);
+  if constexpr (ST == 1 && !(Q == 19 && COLL == 1)) {
+    collide_by_population<Q, COLL, R>(f0, rho1, ux, uy, uz, F1x, F1y, F1z, r);
+    collide_by_population<Q, COLL, R>(f1, rho2, ux, uy, uz, F2x, F2y, F2z, r);
+  } else {
+    collide_component<Q, COLL, R>(f0, rho1, ux, uy, uz, F1x, F1y, F1z, r);
+    collide_component<Q, COLL, R>(f1, rho2, ux, uy, uz, F2x, F2y, F2z, r);
+  }
 }
 
 // ---------------------------------------------------------------------------

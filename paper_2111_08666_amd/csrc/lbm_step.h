@@ -650,7 +650,7 @@ __global__ __launch_bounds__((64 * FusedShape<TY, R, ST, CL>::kNW))
         f1[k][i] = pk[9 + i][lane];
       }
     }
-    collide_node<9, COLL, R>(d, f0[k], f1[k], rho1, rho2, F1x, F1y, R(0), F2x, F2y, R(0));
+    collide_node<9, COLL, ST, R>(d, f0[k], f1[k], rho1, rho2, F1x, F1y, R(0), F2x, F2y, R(0));
     if constexpr (CL) {
       cpop_store<9, ST>(fout, d.cpitch, cidx[k], f0[k], f1[k], (float)rho1, (float)rho2);
     } else {
@@ -846,7 +846,7 @@ __global__ __launch_bounds__(256) void step_d2q9_list(const InstDev *__restrict_
     const R G_ = (R)d.G, gxb = (R)d.gx, gyb = (R)d.gy;
     const R F1x = -G_ * rho1 * sx2 + rho1 * gxb, F1y = -G_ * rho1 * sy2 + rho1 * gyb;
     const R F2x = -G_ * rho2 * sx1 + rho2 * gxb, F2y = -G_ * rho2 * sy1 + rho2 * gyb;
-    collide_node<9, COLL, R>(d, f0, f1, rho1, rho2, F1x, F1y, R(0), F2x, F2y, R(0));
+    collide_node<9, COLL, ST, R>(d, f0, f1, rho1, rho2, F1x, F1y, R(0), F2x, F2y, R(0));
     if constexpr (ST == 0) {
       const uint32_t bo = ((uint32_t)ri * ystride + (uint32_t)x) * 4u;
 #pragma unroll
@@ -1033,7 +1033,7 @@ __global__ __launch_bounds__(256) void step_d3q19(const InstDev *__restrict__ in
         if (L::ez[i]) { sz1 += L::ez[i] * d1; sz2 += L::ez[i] * d2; }
       }
       const R G_ = (R)d.G, gxb = (R)d.gx, gyb = (R)d.gy, gzb = (R)d.gz;
-      collide_node<19, COLL, R>(d, a, b, rho1, rho2, -G_ * rho1 * sx2 + rho1 * gxb,
+      collide_node<19, COLL, ST, R>(d, a, b, rho1, rho2, -G_ * rho1 * sx2 + rho1 * gxb,
                                 -G_ * rho1 * sy2 + rho1 * gyb, -G_ * rho1 * sz2 + rho1 * gzb,
                                 -G_ * rho2 * sx1 + rho2 * gxb, -G_ * rho2 * sy1 + rho2 * gyb,
                                 -G_ * rho2 * sz1 + rho2 * gzb);
@@ -1239,7 +1239,7 @@ __global__ __launch_bounds__(256) void collide_kernel(const InstDev *__restrict_
   if (info & (kInlet | kOutlet)) complete<Q, ST, R>(d, fin, info, x, y, z, a, b);
   const R rho1 = sum_q<Q, R>(a), rho2 = sum_q<Q, R>(b);
   const R G_ = (R)d.G, gxb = (R)d.gx, gyb = (R)d.gy, gzb = (R)d.gz;
-  collide_node<Q, COLL, R>(d, a, b, rho1, rho2, -G_ * rho1 * sx2 + rho1 * gxb, -G_ * rho1 * sy2 + rho1 * gyb,
+  collide_node<Q, COLL, ST, R>(d, a, b, rho1, rho2, -G_ * rho1 * sx2 + rho1 * gxb, -G_ * rho1 * sy2 + rho1 * gyb,
                            -G_ * rho1 * sz2 + rho1 * gzb, -G_ * rho2 * sx1 + rho2 * gxb,
                            -G_ * rho2 * sy1 + rho2 * gyb, -G_ * rho2 * sz1 + rho2 * gzb);
   pop_store<Q, ST, Q == 19>(fout, d.pitch, uniform64(y * d.ystride + z * d.zstride), x, a, b, (float)rho1,
@@ -1413,7 +1413,7 @@ __global__ __launch_bounds__(256) void ccollide_kernel(const InstDev *__restrict
   cpull<Q, ST, R>(d, G(d.f[parity]), info, y, z, c, scs, a, b);
   const R rho1 = sum_q<Q, R>(a), rho2 = sum_q<Q, R>(b);
   const R G_ = (R)d.G, gxb = (R)d.gx, gyb = (R)d.gy, gzb = (R)d.gz;
-  collide_node<Q, COLL, R>(d, a, b, rho1, rho2, -G_ * rho1 * sx2 + rho1 * gxb, -G_ * rho1 * sy2 + rho1 * gyb,
+  collide_node<Q, COLL, ST, R>(d, a, b, rho1, rho2, -G_ * rho1 * sx2 + rho1 * gxb, -G_ * rho1 * sy2 + rho1 * gyb,
                            -G_ * rho1 * sz2 + rho1 * gzb, -G_ * rho2 * sx1 + rho2 * gxb,
                            -G_ * rho2 * sy1 + rho2 * gyb, -G_ * rho2 * sz1 + rho2 * gzb);
   cpop_store<Q, ST, Q == 19>(G(d.f[parity ^ 1]), d.cpitch, c, a, b, (float)rho1, (float)rho2);
@@ -1645,7 +1645,7 @@ __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(3))
               [&](int s_, int i) { return frz[(int64_t)(s_ * Q + i) * nt + t]; });
         }
         const R rho1 = sum_q<Q, R>(a), rho2 = sum_q<Q, R>(b);
-        collide_node<Q, COLL, R>(d, a, b, rho1, rho2, -G_ * rho1 * sx2 + rho1 * gxb, -G_ * rho1 * sy2 + rho1 * gyb,
+        collide_node<Q, COLL, 0, R>(d, a, b, rho1, rho2, -G_ * rho1 * sx2 + rho1 * gxb, -G_ * rho1 * sy2 + rho1 * gyb,
                                  -G_ * rho1 * sz2 + rho1 * gzb, -G_ * rho2 * sx1 + rho2 * gxb,
                                  -G_ * rho2 * sy1 + rho2 * gyb, -G_ * rho2 * sz1 + rho2 * gzb);
 #pragma unroll
