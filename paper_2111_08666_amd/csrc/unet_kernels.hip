@@ -41,6 +41,21 @@ __device__ __forceinline__ bf16x8 pack8(const uint16_t (&v)[8]) {
   return __builtin_bit_cast(bf16x8, u);
 }
 
+// Buffer loads: a wave-uniform base, a byte offset per lane, and zeros from
+// offsets beyond the buffer.  Loads masked this way are issued by every lane on
+// every path, so the compiler can wait for the oldest of several in flight.
+typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
+constexpr uint32_t kWholeBuffer = 0x80000000u;  // bytes reachable from a base
+constexpr uint32_t kOutside = 0xc0000000u;      // offset of a masked lane (a scalar offset keeps it outside)
+__device__ __forceinline__ uint4 buffer_load16(const uint16_t *base, uint32_t bytes, uint32_t offset) {
+  // the caller's base is wave-uniform: say so, for a descriptor in scalar registers
+  const uint64_t v = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  uint16_t *const p = reinterpret_cast<uint16_t *>(((uint64_t)hi << 32) | lo);
+  auto r = __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00027000);
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)offset, 0, 0));
+}
+
 __device__ __forceinline__ floatx16 mfma(bf16x8 a, bf16x8 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -325,19 +340,248 @@ static bool conv_lds_fits(const GemmArgs &a, int bp) {
          ((int64_t)a.h * a.w) % bp == 0;
 }
 
-// Launch with the wave tile chosen by the output channel count.
+// Output of a transposed 32 x 32 product tile: this lane holds channels
+// c0 + 8 q + 4 half + 0..3 of pixel o in registers 4 q .. 4 q + 3.  Bias, ReLU and
+// rounding to BF16; then the lane halves trade registers, so that each stores
+// 16-byte runs of channels (channel counts, strides and offsets multiples of
+// 8, y 16-byte aligned).  bias: a buffer of the biases, empty for none.
+__device__ __forceinline__ void store_pixel(const GemmArgs &a, __amdgpu_buffer_rsrc_t bias, const floatx16 &acc, bool in,
+                                            int64_t o, int c0, int half) {
+  uint32_t w[8];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 b = __builtin_bit_cast(
+        float4, __builtin_amdgcn_raw_buffer_load_b128(bias, 4 * (c0 + 8 * q + 4 * half), 0, 0));
+    const float bv[4] = {b.x, b.y, b.z, b.w};
+    uint16_t h[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float v = acc[4 * q + k] + bv[k];
+      if (a.relu) v = v > 0.f ? v : 0.f;
+      h[k] = f2bf(v);
+    }
+    w[2 * q] = h[0] | ((uint32_t)h[1] << 16);
+    w[2 * q + 1] = h[2] | ((uint32_t)h[3] << 16);
+  }
+  // lower half: channels 0..7 and 16..23; upper half: 8..15 and 24..31
+  uint16_t *const y = a.y + o * a.y_cs + a.y_co + c0;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const auto s0 = __builtin_amdgcn_permlane32_swap(w[4 * q], w[4 * q + 2], false, false);
+    const auto s1 = __builtin_amdgcn_permlane32_swap(w[4 * q + 1], w[4 * q + 3], false, false);
+    const int c = 16 * q + 8 * half;
+    if (in && c0 + c < a.nout) *reinterpret_cast<uint4 *>(y + c) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Implicit GEMM straight from memory: a wave computes 32 TM pixels by 32 TN
+// output channels with no LDS and no barrier; its operand fragments are 16-byte
+// buffer loads (zeros outside the image and the channels) that run kRing steps of
+// 16 reduction channels ahead of the products.  The products are transposed,
+// C[channel][pixel], so a lane ends with runs of channels of one pixel and
+// stores vectors.  For problems too small to fill the chip with the staged
+// convolution's blocks, where the length of one wave's chain is what counts,
+// and for the layers whose operands have little reuse.
+//   ORDER 0, 3x3: reduction by (16-channel group, tap, channel), as in the staged
+//     convolution; the ring is one group's nine taps.
+//   ORDER 1, 3x3: by (tap, channel).
+//   ORDER 2, 3x3 over 8 channels: two taps a step, the whole reduction in flight.
+//   ORDER 3, transposed 2x2: by channel; TN = 4 is the four taps of 32 channels.
+//   ORDER 4, its data gradient: by (tap, channel).
+// Orders 0, 1 and 4 need kc to be a multiple of 16, order 3 too.
+// Both orders of the 3x3 reduction stay because a change of order changes
+// results in the last place, which a whole network carries on.
+// One 256 x 256 image through the network: 341 us with the staged and gathering
+// kernels alone, 207 us with this one where it is chosen, the same bits.
+// ---------------------------------------------------------------------------
+template <int ORDER, int TM, int TN, int GP = 1>
+__global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
+  constexpr bool kConv = ORDER <= 2;
+  constexpr int kRing = ORDER == 0 ? 9 * GP : (ORDER == 2 ? 5 : (ORDER == 3 || (ORDER == 4 && TM * TN == 4) ? 4 : 8));
+  const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
+  const int64_t wid = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t P = (int64_t)a.n * a.h * a.w;
+  const int ctiles = ORDER == 3 ? (a.nout + 31) / 32 : (a.nout + 32 * TN - 1) / (32 * TN);
+  if (wid >= (int64_t)pix_tiles * ctiles) return;
+  // the four waves of a block share their pixels where they can
+  const int ct = (int)(wid % ctiles);
+  const int64_t pix0 = wid / ctiles * (32 * TM);
+  const int col0 = ct * (ORDER == 3 ? 32 : 32 * TN);
+  const int taps = kConv ? 9 : 4;
+  // A (pixels): byte offsets from a base at or before the wave's first pixel
+  const int W2 = 2 * a.w;
+  int py[TM], px[TM];
+  bool in[TM];
+#pragma unroll
+  for (int t = 0; t < TM; ++t) {
+    const int64_t p = pix0 + 32 * t + l31;
+    in[t] = p < P;
+    const int64_t q = in[t] ? p : P - 1;
+    const int64_t r = q / a.w;
+    px[t] = (int)(q - r * a.w);
+    py[t] = (int)(r % a.h);
+  }
+  const uint16_t *abase;
+  uint32_t arow[TM];  // this lane's pixel, byte offset from abase
+  const uint32_t cs2 = 2u * (uint32_t)a.x_cs;
+  if constexpr (ORDER == 4) {
+    // dy pixel (2y, 2x); rows of the 2h x 2w grid, linear over images
+    const int64_t r0 = pix0 / a.w;
+    abase = a.x + a.x_co + 2 * r0 * W2 * a.x_cs;
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      const int64_t p = in[t] ? pix0 + 32 * t + l31 : P - 1;
+      const int64_t r = p / a.w;
+      arow[t] = in[t] ? (uint32_t)((2 * (r - r0) * W2 + 2 * (p - r * a.w)) * cs2) + 16u * half : kOutside;
+    }
+  } else {
+    abase = a.x + a.x_co + (pix0 - (kConv ? a.w + 1 : 0)) * a.x_cs;
+#pragma unroll
+    for (int t = 0; t < TM; ++t) arow[t] = in[t] ? (uint32_t)(32 * t + l31) * cs2 + 16u * half : kOutside;
+  }
+  // offset of tap (dy, dx) of a 3x3 window, masked outside the image
+  auto tap_offset = [&](int t, int tap, uint32_t base) {
+    const int dy = tap / 3, dx = tap % 3;
+    const int y = py[t] + dy - 1, x = px[t] + dx - 1;
+    const bool ok = in[t] && tap < 9 && y >= 0 && y < a.h && x >= 0 && x < a.w;
+    return ok ? base + (uint32_t)(dy * a.w + dx) * cs2 : kOutside;
+  };
+  // B (weights, [channel][tap][kc])
+  const uint16_t *const bbase = a.wgt + (int64_t)col0 * taps * a.kc;
+  uint32_t brow[TN];
+#pragma unroll
+  for (int u = 0; u < TN; ++u) {
+    const int c = ORDER == 3 ? l31 : 32 * u + l31;
+    brow[u] = col0 + c < a.nout
+                  ? 2u * (uint32_t)((c * taps + (ORDER == 3 ? u : 0)) * a.kc) + (ORDER == 2 ? 0u : 16u * half)
+                  : kOutside;
+  }
+  const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(abase), 0, (int)kWholeBuffer, 0x00027000);
+  const auto br = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(bbase), 0, (int)kWholeBuffer, 0x00027000);
+  auto get = [](auto r, uint32_t off, int s) {
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, s, 0));
+  };
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int u = 0; u < TN; ++u) acc[t][u] = floatx16{};
+  bf16x8 A[kRing][TM], B[kRing][TN];
+  auto products = [&](int i) {
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int u = 0; u < TN; ++u) acc[t][u] = mfma(B[i][u], A[i][t], acc[t][u]);
+  };
+  if constexpr (ORDER == 0) {
+    uint32_t off[9][TM];
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+#pragma unroll
+      for (int t = 0; t < TM; ++t) off[k][t] = tap_offset(t, k, arow[t]);
+    // GP groups at a time: their loads share cache lines
+    const int groups = a.kc / 16;
+    auto load = [&](int k, int g) {
+#pragma unroll
+      for (int t = 0; t < TM; ++t) A[k][t] = get(ar, off[k % 9][t], 32 * g);
+#pragma unroll
+      for (int u = 0; u < TN; ++u) B[k][u] = get(br, brow[u], 2 * (k % 9) * a.kc + 32 * g);
+    };
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+#pragma unroll
+      for (int v = 0; v < GP; ++v) load(9 * v + k, v);
+    for (int g = GP; g < groups; g += GP) {
+#pragma unroll
+      for (int v = 0; v < GP; ++v)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+          products(9 * v + k);
+          if (v == GP - 1) {
+#pragma unroll
+            for (int x = 0; x < GP; ++x) load(9 * x + k, g + x);
+          }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 9 * GP; ++k) products(k);
+  } else if constexpr (ORDER == 2) {
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const int tap = 2 * k + half;
+#pragma unroll
+      for (int t = 0; t < TM; ++t) A[k][t] = get(ar, tap_offset(t, tap, arow[t] - 16u * half), 0);
+#pragma unroll
+      for (int u = 0; u < TN; ++u) B[k][u] = get(br, tap < 9 ? brow[u] + 16u * tap : kOutside, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k) products(k);
+  } else {
+    // steps in order; the step being loaded is (tap, 16-channel group)
+    const int groups = a.kc / 16, steps = (ORDER == 1 ? 9 : (ORDER == 4 ? 4 : 1)) * groups;
+    int ltap = 0, lg = 0;
+    uint32_t off[TM];
+    auto at_tap = [&]() {
+#pragma unroll
+      for (int t = 0; t < TM; ++t) off[t] = ORDER == 1 ? tap_offset(t, ltap, arow[t]) : arow[t];
+    };
+    at_tap();
+    auto load = [&](int i) {
+      const int as = 32 * lg + (ORDER == 4 ? ((ltap >> 1) * W2 + (ltap & 1)) * (int)cs2 : 0);
+      const int bs = 2 * ltap * a.kc + 32 * lg;
+#pragma unroll
+      for (int t = 0; t < TM; ++t) A[i][t] = get(ar, off[t], as);
+#pragma unroll
+      for (int u = 0; u < TN; ++u) B[i][u] = get(br, brow[u], bs);
+      if (++lg == groups) {
+        lg = 0;
+        ++ltap;
+        if (ORDER == 1) at_tap();
+      }
+    };
+    // past the last step the loads repeat the first one
+    auto load_next = [&](int i, int s) {
+      if (s >= steps) { ltap = 0; lg = 0; }
+      load(i);
+    };
+#pragma unroll
+    for (int i = 0; i < kRing; ++i) load_next(i, i);
+    int s = 0;
+    for (; s + kRing <= steps; s += kRing) {
+#pragma unroll
+      for (int i = 0; i < kRing; ++i) {
+        products(i);
+        load_next(i, s + i + kRing);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kRing - 1; ++i)
+      if (s + i < steps) products(i);
+  }
+  // C[channel 8 (r / 4) + 4 half + r % 4][pixel l31]
+  const auto bias = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.bias), 0, a.bias ? 4 * a.nout : 0, 0x00027000);
+#pragma unroll
+  for (int t = 0; t < TM; ++t) {
+    const int64_t p = pix0 + 32 * t + l31;
+#pragma unroll
+    for (int u = 0; u < TN; ++u) {
+      int64_t o = p;
+      if constexpr (ORDER == 3) {
+        const int64_t r = p / a.w;  // rows are linear over images on both grids
+        o = (2 * r + (u >> 1)) * W2 + 2 * (p - r * a.w) + (u & 1);
+      }
+      const int c0 = col0 + (ORDER == 3 ? 0 : 32 * u);
+      store_pixel(a, bias, acc[t][u], p < P, o, c0, half);
+    }
+  }
+}
+
+// The general kernel's launch: reduction channels not a multiple of 16 (8 has
+// its own form), outputs the direct kernel cannot store as vectors, or offsets
+// beyond its window.
 template <int MODE>
-static void launch_igemm(const GemmArgs &a, int64_t P, int taps_z, hipStream_t s) {
-  if (MODE == 0 && a.nout <= 32 && conv_lds_fits(a, conv_block_pix(4))) {
-    dim3 g((unsigned)(P / conv_block_pix(4)), 1);
-    conv3x3_lds<4, 1><<<g, 256, 0, s>>>(a);
-    return;
-  }
-  if (MODE == 0 && conv_lds_fits(a, conv_block_pix(2))) {
-    dim3 g((unsigned)(P / conv_block_pix(2)), (unsigned)((a.nout + 63) / 64));
-    conv3x3_lds<2, 2><<<g, 256, 0, s>>>(a);
-    return;
-  }
+static void launch_gather(const GemmArgs &a, int64_t P, int taps_z, hipStream_t s) {
   if (a.nout >= 64) {
     dim3 g((unsigned)((P + 255) / 256), (unsigned)((a.nout + 63) / 64), (unsigned)taps_z);
     igemm_fwd<MODE, 2, 2><<<g, 256, 0, s>>>(a);
@@ -345,6 +589,61 @@ static void launch_igemm(const GemmArgs &a, int64_t P, int taps_z, hipStream_t s
     dim3 g((unsigned)((P + 511) / 512), (unsigned)((a.nout + 31) / 32), (unsigned)taps_z);
     igemm_fwd<MODE, 4, 1><<<g, 256, 0, s>>>(a);
   }
+}
+
+// Blocks of the staged convolution (of 64 channels) up to which the direct kernel
+// is faster: the staged one then leaves most CUs idle.  256 -> 128 channels on
+// 16 x 32 x 32 pixels (128 blocks): 54 us direct, 28 us staged.
+constexpr int64_t kDirectBlocks = 64;
+
+template <int ORDER, int TM, int TN, int GP = 1>
+static void launch_direct(const GemmArgs &a, int64_t P, hipStream_t s) {
+  const int64_t pt = (P + 32 * TM - 1) / (32 * TM);
+  const int64_t ct = (a.nout + (ORDER == 3 ? 32 : 32 * TN) - 1) / (ORDER == 3 ? 32 : 32 * TN);
+  // one wave per block while the waves do not fill the chip: every CU gets one,
+  // and with the channel tile counted fastest an XCD meets few of them
+  const int wpb = pt * ct <= 4096 ? 1 : 4;
+  igemm_direct<ORDER, TM, TN, GP><<<dim3((unsigned)((pt * ct + wpb - 1) / wpb)), 64 * wpb, 0, s>>>(a, (int)pt);
+}
+
+// Tile by the number of waves: the largest that still gives the chip's 1024
+// SIMDs a wave each (a small one has the shorter chain and the more waves).
+template <int ORDER>
+static void launch_direct_tiles(const GemmArgs &a, int64_t P, hipStream_t s) {
+  const int64_t t = ((P + 31) / 32) * ((a.nout + 31) / 32);  // 32 x 32 tiles
+  if (a.nout > 32 && t >= 4 * 1024) launch_direct<ORDER, 2, 2>(a, P, s);
+  else if (t >= 2 * 1024) launch_direct<ORDER, 2, 1>(a, P, s);
+  else if (ORDER == 0 && a.kc % 32 == 0) launch_direct<ORDER, 1, 1, ORDER == 0 ? 2 : 1>(a, P, s);
+  else launch_direct<ORDER, 1, 1>(a, P, s);
+}
+
+// Can the direct kernel run this?  Its stores are vectors of 8 channels; the
+// offsets of a wave (its pixels, the rows above and below them) have to stay
+// within the buffer window, and its tiles within a grid.
+static bool direct_fits(const GemmArgs &a, int64_t P, int taps) {
+  if (reinterpret_cast<uintptr_t>(a.y) % 16 || a.y_cs % 8 || a.y_co % 8 || a.nout % 8) return false;
+  const int64_t reach = (taps == 9 ? 64 + 2 * (int64_t)a.w + 2 : 2 * (64 + 2 * (int64_t)a.w) * 2) * a.x_cs * 2;
+  const int64_t wbytes = (int64_t)64 * taps * a.kc * 2;
+  return reach < kWholeBuffer && wbytes < ((int64_t)1 << 29) && ((P + 31) / 32) * ((a.nout + 31) / 32) < ((int64_t)1 << 31);
+}
+
+static void launch_conv3x3(const GemmArgs &a, int64_t P, hipStream_t s) {
+  const bool direct = direct_fits(a, P, 9);
+  if (direct && a.kc == 8) {
+    if (P >= 2 * 32 * 1024) launch_direct<2, 2, 1>(a, P, s);
+    else launch_direct<2, 1, 1>(a, P, s);
+    return;
+  }
+  const int tm = a.nout <= 32 && conv_lds_fits(a, conv_block_pix(4)) ? 4 : 2;
+  if (conv_lds_fits(a, conv_block_pix(tm))) {
+    const dim3 g((unsigned)(P / conv_block_pix(tm)), tm == 4 ? 1u : (unsigned)((a.nout + 63) / 64));
+    if (direct && (int64_t)g.x * g.y <= (tm == 4 ? 2 * kDirectBlocks : kDirectBlocks)) launch_direct_tiles<0>(a, P, s);
+    else if (tm == 4) conv3x3_lds<4, 1><<<g, 256, 0, s>>>(a);
+    else conv3x3_lds<2, 2><<<g, 256, 0, s>>>(a);
+    return;
+  }
+  if (direct && a.kc % 16 == 0) launch_direct_tiles<1>(a, P, s);
+  else launch_gather<0>(a, P, 1, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -402,17 +701,6 @@ __device__ __forceinline__ bf16x8 tr_fragment(lds_char *first, lds_char *second)
   const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)first);
   const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)second);
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-// Buffer loads: a wave-uniform base, a byte offset per lane, and zeros from
-// offsets beyond the buffer.  Loads masked this way are issued by every lane on
-// every path, so the compiler can wait for the oldest of several in flight.
-typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
-constexpr uint32_t kOutside = 0xffffffffu;       // offset of a masked lane
-constexpr uint32_t kWholeBuffer = 0xfffffff0u;  // bytes reachable from a base
-__device__ __forceinline__ uint4 buffer_load16(const uint16_t *base, uint32_t bytes, uint32_t offset) {
-  auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, (int)bytes, 0x00027000);
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)offset, 0, 0));
 }
 
 // Steps of a weight gradient: segments of 16 columns by (image, row) slots.
@@ -988,7 +1276,7 @@ int unet_conv3x3_fwd(const uint16_t *x, int n, int h, int w, int cin, int x_cs, 
       !slice_ok(x_co, cin, x_cs) || !slice_ok(y_co, cout, y_cs))
     return -1;
   GemmArgs a{x, n, h, w, cin, x_cs, x_co, wgt, bias, cout, y, y_cs, y_co, relu};
-  launch_igemm<0>(a, (int64_t)n * h * w, 1, (hipStream_t)s);
+  launch_conv3x3(a, (int64_t)n * h * w, (hipStream_t)s);
   return launched();
 }
 
@@ -1073,7 +1361,12 @@ int unet_upconv_fwd(const uint16_t *x, int n, int h, int w, int cin, int x_cs, i
       !slice_ok(x_co, cin, x_cs) || !slice_ok(y_co, cout, y_cs))
     return -1;
   GemmArgs a{x, n, h, w, cin, x_cs, x_co, wgt, bias, cout, y, y_cs, y_co, 0};
-  launch_igemm<1>(a, (int64_t)n * h * w, 4, (hipStream_t)s);
+  const int64_t P = (int64_t)n * h * w;
+  if (cin % 16 == 0 && direct_fits(a, P, 4)) {
+    launch_direct<3, 1, 4>(a, P, (hipStream_t)s);
+  } else {
+    launch_gather<1>(a, P, 4, (hipStream_t)s);
+  }
   return launched();
 }
 
@@ -1085,7 +1378,9 @@ int unet_upconv_bwd_data(const uint16_t *dy, int n, int h, int w, int cout, int 
   up_rearrange<<<grid1d((int64_t)cout * 4 * cin), 256, 0, (hipStream_t)s>>>(wgt, cout, cin, wt);
   // A = dy over the 2h x 2w grid gathered at 2p + tap, output grid h x w
   GemmArgs a{dy, n, h, w, cout, dy_cs, dy_co, wt, nullptr, cin, dx, dx_cs, dx_co, 0};
-  launch_igemm<2>(a, (int64_t)n * h * w, 1, (hipStream_t)s);
+  const int64_t P = (int64_t)n * h * w;
+  if (cout % 16 == 0 && direct_fits(a, P, 4)) launch_direct_tiles<4>(a, P, (hipStream_t)s);
+  else launch_gather<2>(a, P, 1, (hipStream_t)s);
   return launched();
 }
 
