@@ -667,7 +667,7 @@ struct WgradArgs {
 };
 
 // ---------------------------------------------------------------------------
-// Weight gradients with all taps in one wave.  A wave owns a 32 x 32 tile of
+// Weight gradients with all taps in one wave, for images of any width.  A wave owns a 32 x 32 tile of
 // (output, input) channels and marches down image rows, 16 pixels of a row
 // at a time, accumulating every tap of that tile: a row of x enters three
 // products per column shift (with the dy rows above, at and below it), so its
@@ -915,6 +915,324 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_taps(WgradArgs a, int kb, in
       for (int t = 0; t < ntap; ++t) a.bpartial[((int64_t)ck * ntap + t) * a.cout + m0 + tid] = t ? 0.f : r;
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradients in pixel order, for images of whole 16-pixel segments up to
+// 256 (MODE 1: 128) columns.  One accumulator takes a tap's products of 4096
+// pixels in the order they lie in memory, and the bias its pixel pairs, so a
+// gradient does not depend on how many waves shared the work (Adam's first steps
+// turn a last-place change of a vanishing gradient into a whole learning rate).
+// A block owns one such share of the pixels and a 32 x 32 channel tile.  Rows of
+// x and dy go through LDS in stages of at most SP pixels, whole rows with a zero
+// column on both sides, x in a ring that also holds the rows above and below the
+// stage; a row outside its image is read from a block of zeros.
+// The sums are serial chains, so what counts is that nothing else delays them:
+// four waves multiply and four stage, one of each per SIMD, a stage ahead and its
+// loads two further.  MODE 0: a wave owns the three taps of a row (three reads of
+// four pixels serve all three: the outer two taps are register pairs of them, the
+// middle one is shifted by half a register) and a fourth adds up the bias.
+// MODE 1: a wave per tap.
+// 64 -> 64 channels, 16 x 128 x 128: 118 us with a block per tap, 32 us so (45 us
+// with ten waves that each stage, multiply one tap and read both operands).  The
+// chain of 256 steps of three products is 10 us, staging alone 17 us.
+// ---------------------------------------------------------------------------
+constexpr int kWgRowsThreads = 512;
+
+template <int MODE, int SP, int SEGS>
+__global__ __launch_bounds__(kWgRowsThreads) void wgrad_rows(WgradArgs a, int kb, int chunk_rows, int stage_rows,
+                                                             int ci_tiles, int tiles) {
+  constexpr int NA = MODE == 0 ? 1 : 4;  // dy tiles per stage
+  constexpr int NT = MODE == 0 ? 3 : 1;  // taps of a wave
+  constexpr int kPass = 64;              // pixels the staging waves take at a time
+  constexpr int NP = SP / kPass;         // pieces of a tile a thread stages
+  constexpr int kTile = SP * kPixBytes;
+  constexpr int U = SEGS < 4 ? 4 : SEGS;  // steps per turn of the loop
+  // x: MODE 0 a ring of 2 stage_rows + 2 rows of w + 2 pixels (largest for
+  // one-row stages; its last row is read two pixels further), MODE 1 two stages
+  constexpr int kX = MODE == 0 ? 4 * (SP + 2) * kPixBytes : 2 * kTile;
+  constexpr int kZeroPix = 16 * SEGS + 4;  // a unit of zero pixels
+  constexpr int kZero = kX + 2 * NA * kTile;
+  constexpr int kSpare = kZero + kZeroPix * kPixBytes;
+  __shared__ __attribute__((aligned(16))) char smem[kSpare + 16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  lds_char *const lds = (lds_char *)smem;
+  const int bid = blockIdx.x;
+  const bool by8 = (kb & 7) == 0;  // blocks of one share on one XCD
+  const int ck = by8 ? (bid / (8 * tiles)) * 8 + (bid & 7) : bid % kb;
+  const int tile = by8 ? (bid >> 3) % tiles : bid / kb;
+  const int m0 = (tile / ci_tiles) * 32, n0 = (tile % ci_tiles) * 32;
+  const bool bias = a.bpartial && n0 == 0;
+  const int w = a.w, G = stage_rows, ring = 2 * G + 2, pitch = (w + 2) * kPixBytes;
+  const int rows_all = a.n * a.h;
+  const int r0 = ck * chunk_rows, r1 = r0 + chunk_rows < rows_all ? r0 + chunk_rows : rows_all;
+  const int stages = r1 > r0 ? (r1 - r0 + G - 1) / G : 0;
+  const uint16_t *const xg = a.x + a.x_co + n0, *const dg = a.dy + a.dy_co + m0;
+
+  // zero columns, the block of zeros, and the rows above the first stage and its
+  // first one (ring rows 0 and 1)
+  const uint4 zero = make_uint4(0, 0, 0, 0);
+  for (int e = tid; e < 4 * kZeroPix; e += kWgRowsThreads) *reinterpret_cast<uint4 *>(smem + kZero + 16 * e) = zero;
+  if constexpr (MODE == 0) {
+    for (int e = tid; e < ring * 8; e += kWgRowsThreads)
+      *reinterpret_cast<uint4 *>(smem + (e >> 3) * pitch + ((e >> 2) & 1) * (w + 1) * kPixBytes + 16 * (e & 3)) = zero;
+    if (stages > 0)
+      for (int e = tid; e < 2 * w * 4; e += kWgRowsThreads) {
+        const int p = e >> 2, q = p / w;
+        const int64_t r = r0 - 1 + q;
+        uint4 v = zero;
+        if (n0 + 8 * (e & 3) < a.cin && r >= 0)
+          v = *reinterpret_cast<const uint4 *>(xg + (r * w + p - q * w) * a.x_cs + 8 * (e & 3));
+        *reinterpret_cast<uint4 *>(smem + q * pitch + (1 + p - q * w) * kPixBytes + 16 * (e & 3)) = v;
+      }
+  }
+
+  if (wave >= 4) {  // staging: piece k of this thread is 8 channels (ch) of one pixel of a stage
+    const int t0 = tid - 256, ch = 8 * (t0 & 3);
+    const bool xc = n0 + ch < a.cin, dc = m0 + ch < a.cout;
+    uint32_t xoff[NP], doff[NP];
+    int lx[NP], ld[NP];  // LDS addresses; a piece past the stage's pixels goes to a spare one
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      const int p = (t0 >> 2) + kPass * k;
+      const bool in = p < G * w;
+      const int prow = p / w, col = p - prow * w;
+      // MODE 0: stage 0 goes to ring rows 2 .. (G = 1: 2 and 3 of 4)
+      lx[k] = !in ? kSpare : (MODE == 0 ? (2 + prow) * pitch + (1 + col) * kPixBytes : p * kPixBytes) + 2 * ch;
+      ld[k] = !in ? kSpare : kX + p * kPixBytes + 2 * ch;
+      xoff[k] = xc && in ? 2u * (uint32_t)(p * a.x_cs + ch) : kOutside;
+      doff[k] = dc && in ? 2u * (uint32_t)((MODE == 0 ? p : 4 * w * prow + 2 * col) * a.dy_cs + ch) : kOutside;
+    }
+    struct Staged {
+      uint4 x[NP], dy[NA][NP];
+    } st[2];
+    // stage i: dy rows r0 + i G ..; x rows the same (MODE 1) or one further on.
+    // Rows past the share's last (x: the one below it) lie beyond the buffer.
+    const uint32_t xrow = 2u * (uint32_t)(w * a.x_cs), drow = 2u * (uint32_t)((MODE == 0 ? w : 4 * w) * a.dy_cs);
+    const int xlast = MODE == 0 && r1 < rows_all ? r1 + 1 : r1;
+    auto load = [&](int i, Staged &g) __attribute__((always_inline)) {
+      const int dr = r0 + i * G, xr = dr + (MODE == 0 ? 1 : 0);
+      const int dn = r1 - dr, xn = xlast - xr;
+      const uint32_t xbytes = (uint32_t)(xn < 0 ? 0 : xn < G ? xn : G) * xrow;
+      const uint32_t dbytes = (uint32_t)(dn < 0 ? 0 : dn < G ? dn : G) * drow;
+      const uint16_t *const xp = xg + (int64_t)xr * (xrow / 2);
+      const uint16_t *const dp = dg + (int64_t)dr * (drow / 2);
+#pragma unroll
+      for (int k = 0; k < NP; ++k) g.x[k] = buffer_load16(xp, xbytes, xoff[k]);
+#pragma unroll
+      for (int t = 0; t < NA; ++t) {
+        const int tap = MODE == 0 ? 0 : (2 * w * (t >> 1) + (t & 1)) * a.dy_cs;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) g.dy[t][k] = buffer_load16(dp + tap, dbytes, doff[k]);
+      }
+    };
+    auto put = [&](int odd, const Staged &g) __attribute__((always_inline)) {
+      // (no branch may part these waits from the loads they count)
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        const bool in = ld[k] != kSpare;
+        *reinterpret_cast<uint4 *>(smem + lx[k] + (MODE == 1 && in ? odd * kTile : 0)) = g.x[k];
+#pragma unroll
+        for (int t = 0; t < NA; ++t)
+          *reinterpret_cast<uint4 *>(smem + ld[k] + (in ? (odd * NA + t) * kTile : 0)) = g.dy[t][k];
+        if (MODE == 0 && in) {  // G rows on in the ring
+          lx[k] += G * pitch;
+          lx[k] = lx[k] >= ring * pitch ? lx[k] - ring * pitch : lx[k];
+        }
+      }
+    };
+    load(0, st[0]);
+    load(1, st[1]);
+    put(0, st[0]);
+    load(2, st[0]);
+    __syncthreads();
+    for (int i = 0; i < stages; i += 2) {  // stages past the last are zeros
+      put(1, st[1]);
+      load(i + 3, st[1]);
+      __syncthreads();
+      put(0, st[0]);
+      load(i + 4, st[0]);
+      __syncthreads();
+    }
+    return;
+  }
+
+  const int lo = tr_pixel(lane) * kPixBytes + tr_channel_bytes(lane);
+  const int segs = w >> 4, steps = G * segs;
+  // bias: a chain of pixel pairs per channel; both lane halves hold the same sum
+  float bsum = 0.f;
+  auto add_bias = [&](const bf16x8 &F) __attribute__((always_inline)) {
+    const uint4 v = __builtin_bit_cast(uint4, F);
+    const uint32_t d4[4] = {v.x, v.y, v.z, v.w};
+    float lo8[4], hi8[4];  // pairs of pixels 0 .. 7 and 8 .. 15
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t s = __float_as_uint(__uint_as_float(d4[q] << 16) + __uint_as_float(d4[q] & 0xffff0000u));
+      const auto h = __builtin_amdgcn_permlane32_swap(s, s, false, false);
+      lo8[q] = __uint_as_float(h[0]);
+      hi8[q] = __uint_as_float(h[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bsum += lo8[q];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bsum += hi8[q];
+  };
+  const int ntap = MODE == 1 ? 4 : 1;
+  const int64_t share = (int64_t)ck * ntap;
+
+  if (MODE == 0 && wave == 3) {
+    __syncthreads();
+    for (int i = 0; i < stages; i += 2) {
+#pragma unroll
+      for (int odd = 0; odd < 2; ++odd) {
+        if (bias) {
+          bf16x8 F[2][4];
+          int s = 0;
+          auto fetch4 = [&](bf16x8 (&f)[4]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v, ++s) {
+              lds_char *const p = lds + (s < steps ? kX + odd * kTile + s * 16 * kPixBytes : kZero) + lo;
+              f[v] = tr_fragment(p, p + 4 * kPixBytes);
+            }
+          };
+          fetch4(F[0]);
+          for (int u = 0; u < steps; u += 8) {
+            fetch4(F[1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) add_bias(F[0][v]);
+            fetch4(F[0]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) add_bias(F[1][v]);
+          }
+        }
+        __syncthreads();
+      }
+    }
+    if (bias && lane < 32 && m0 + lane < a.cout) a.bpartial[share * a.cout + m0 + lane] = bsum;
+    return;
+  }
+
+  floatx16 acc[NT] = {};
+  int xr = 0;        // ring row of the row above the stage's first
+  int y = r0 % a.h;  // row within its image
+  __syncthreads();
+  auto stage = [&](int i, int odd) __attribute__((always_inline)) {
+    const int nr = r1 - (r0 + i * G) < G ? r1 - (r0 + i * G) : G;
+    // position of the next unit of SEGS steps to fetch
+    const int parts = MODE == 0 ? segs / SEGS : 1;
+    int part = 0, row = 0, yy = y, slot = 0, done = 0;
+    auto row_start = [&]() {  // this wave's window row of image row yy
+      if constexpr (MODE == 0) {
+        const int s = xr + row + wave;
+        const bool in = yy + wave - 1 >= 0 && yy + wave - 1 < a.h && row < nr;
+        slot = in ? (s >= ring ? s - ring : s) * pitch : -1;
+      }
+    };
+    row_start();
+    const int dy0 = kX + (odd * NA + (MODE == 0 ? 0 : wave)) * kTile;
+    int ua = 0, ub = 0;  // the unit's LDS addresses
+    auto next_unit = [&]() __attribute__((always_inline)) {
+      ua = done < steps ? dy0 + done * 16 * kPixBytes : kZero;
+      if constexpr (MODE == 0) {
+        ub = slot < 0 ? kZero : slot + part * (SEGS * 16 * kPixBytes);
+        if (++part == parts) {
+          part = 0;
+          ++row;
+          if (++yy == a.h) yy = 0;
+          row_start();
+        }
+      } else {
+        ub = done < steps ? odd * kTile + done * 16 * kPixBytes : kZero;
+      }
+      done += SEGS;
+    };
+    // Fragments are fetched kAhead steps early, with no condition, so that the
+    // wait before a product is for its own fragments only.
+    constexpr int kAhead = 2, kSlots = 4;
+    bf16x8 A[kSlots];
+    short4v B[kSlots][MODE == 0 ? 3 : 2];
+    auto fetch = [&](int k) __attribute__((always_inline)) {
+      if (k % SEGS == 0) next_unit();
+      lds_char *const p = lds + ua + lo + (k % SEGS) * 16 * kPixBytes;
+      A[k % kSlots] = tr_fragment(p, p + 4 * kPixBytes);
+      lds_char *const q = lds + ub + lo + (k % SEGS) * 16 * kPixBytes;
+#pragma unroll
+      for (int j = 0; j < (MODE == 0 ? 3 : 2); ++j)
+        B[k % kSlots][j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(q + 4 * j * kPixBytes));
+    };
+    auto product = [&](int v) __attribute__((always_inline)) {
+      const bf16x8 f = __builtin_bit_cast(bf16x8, __builtin_shufflevector(B[v][0], B[v][1], 0, 1, 2, 3, 4, 5, 6, 7));
+      acc[0] = mfma(A[v], f, acc[0]);
+      if constexpr (MODE == 0) {  // pixels -1 .. 6 so far; 0 .. 7 and 1 .. 8
+        const short4v b0 = B[v][0], b1 = B[v][1], b2 = B[v][2];
+        const auto r0 = __builtin_bit_cast(uint2, b0), r1 = __builtin_bit_cast(uint2, b1), r2 = __builtin_bit_cast(uint2, b2);
+        const uint4 g = make_uint4(__builtin_amdgcn_alignbit(r0.y, r0.x, 16), __builtin_amdgcn_alignbit(r1.x, r0.y, 16),
+                                   __builtin_amdgcn_alignbit(r1.y, r1.x, 16), __builtin_amdgcn_alignbit(r2.x, r1.y, 16));
+        acc[1] = mfma(A[v], __builtin_bit_cast(bf16x8, g), acc[1]);
+        const uint4 h = make_uint4(r0.y, r1.x, r1.y, r2.x);
+        acc[2] = mfma(A[v], __builtin_bit_cast(bf16x8, h), acc[2]);
+      } else if (bias) {
+        add_bias(A[v]);
+      }
+    };
+#pragma unroll
+    for (int v = 0; v < kAhead; ++v) fetch(v);
+    for (int s = 0; s < steps; s += U) {
+#pragma unroll
+      for (int v = 0; v < U; ++v) {
+        fetch((v + kAhead) % U);
+        __builtin_amdgcn_sched_barrier(0);  // the fetches stay ahead of the products
+        product(v % kSlots);
+      }
+    }
+    __syncthreads();
+    xr += G;
+    xr = xr >= ring ? xr - ring : xr;
+    y += G;
+    if (y >= a.h) y %= a.h;
+  };
+  for (int i = 0; i < stages; i += 2) {
+    stage(i, 0);
+    stage(i + 1, 1);  // past the last: zeros
+  }
+  const int n = n0 + (lane & 31);
+  float *const out = a.partial + share * a.cout * a.ncol;
+  if (n < a.cin) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + c_row(r, lane);
+        if (m >= a.cout) continue;
+        if constexpr (MODE == 0) out[(int64_t)m * a.ncol + (3 * wave + t) * a.cin + n] = acc[t][r];
+        else out[((int64_t)wave * a.cout + m) * a.ncol + n] = acc[t][r];
+      }
+  }
+  if (MODE == 1 && bias && lane < 32 && m0 + lane < a.cout) a.bpartial[(share + wave) * a.cout + m0 + lane] = bsum;
+}
+
+template <int MODE, int SP>
+static void launch_wgrad_rows(const WgradArgs &a, int kb, hipStream_t s) {
+  const int64_t rows = (int64_t)a.n * a.h;
+  const int chunk = kWgradPix % a.w == 0 ? kWgradPix / a.w : (int)((rows + kb - 1) / kb);
+  const int G = SP / a.w;
+  const int ci_tiles = (a.cin + 31) / 32, tiles = ci_tiles * ((a.cout + 31) / 32);
+  const dim3 g((unsigned)((int64_t)kb * tiles));
+  const int segs = MODE == 0 ? a.w / 16 : G * a.w / 16;
+  if (segs % 8 == 0) wgrad_rows<MODE, SP, 8><<<g, kWgRowsThreads, 0, s>>>(a, kb, chunk, G, ci_tiles, tiles);
+  else if (segs % 4 == 0) wgrad_rows<MODE, SP, 4><<<g, kWgRowsThreads, 0, s>>>(a, kb, chunk, G, ci_tiles, tiles);
+  else if (segs % 2 == 0) wgrad_rows<MODE, SP, 2><<<g, kWgRowsThreads, 0, s>>>(a, kb, chunk, G, ci_tiles, tiles);
+  else wgrad_rows<MODE, SP, 1><<<g, kWgRowsThreads, 0, s>>>(a, kb, chunk, G, ci_tiles, tiles);
+}
+
+// Whole 16-pixel segments, rows that fit a stage, and a stage's pixels within
+// the buffer window.
+static bool wgrad_rows_fits(const WgradArgs &a, int sp) {
+  const int64_t cs = a.x_cs > 4 * (int64_t)a.dy_cs ? a.x_cs : 4 * (int64_t)a.dy_cs;
+  return a.w % 16 == 0 && a.w <= sp && (int64_t)a.n * a.h < ((int64_t)1 << 31) - 512 && 2 * (sp + 2) * cs < kWholeBuffer;
 }
 
 template <int MODE>
@@ -1304,7 +1622,8 @@ int unet_conv3x3_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs
   const int kb = (int)((P + kWgradPix - 1) / kWgradPix);
   const int64_t wpart = (int64_t)kb * cout * 9 * cin;
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, 9 * cin, db ? partial + wpart : nullptr};
-  launch_wgrad_taps<0>(a, kb, (hipStream_t)s);
+  if (wgrad_rows_fits(a, 256)) launch_wgrad_rows<0, 256>(a, kb, (hipStream_t)s);
+  else launch_wgrad_taps<0>(a, kb, (hipStream_t)s);
   wgrad_reduce<<<grid1d((int64_t)cout * 9 * cin), 256, 0, (hipStream_t)s>>>(partial, kb, 1, cout, 9 * cin, dw,
                                                                              accumulate);
   if (db) bias_reduce<<<(cout + 63) / 64, 64, 0, (hipStream_t)s>>>(partial + wpart, kb, cout, db, accumulate);
@@ -1393,7 +1712,8 @@ int unet_upconv_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs,
   const int kb = (int)((P + kWgradPix - 1) / kWgradPix);
   const int64_t wpart = (int64_t)kb * 4 * cout * cin;
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, cin, db ? partial + wpart : nullptr};
-  launch_wgrad_taps<1>(a, kb, (hipStream_t)s);
+  if (wgrad_rows_fits(a, 128)) launch_wgrad_rows<1, 128>(a, kb, (hipStream_t)s);
+  else launch_wgrad_taps<1>(a, kb, (hipStream_t)s);
   wgrad_reduce<<<grid1d((int64_t)4 * cout * cin), 256, 0, (hipStream_t)s>>>(partial, kb, 4, cout, cin, dw, 0);
   if (db) bias_reduce<<<(cout + 63) / 64, 64, 0, (hipStream_t)s>>>(partial + wpart, (int64_t)kb * 4, cout, db, 0);
   return launched();

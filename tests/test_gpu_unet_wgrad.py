@@ -53,6 +53,7 @@ def _conv_wgrad(S, x, dy):
 @pytest.mark.parametrize("n,h,w,cin,cout", [
     (1, 1, 1, 8, 8), (3, 1, 1, 40, 8), (5, 3, 2, 8, 40), (2, 17, 16, 32, 32), (40, 4, 4, 16, 72),
     (2, 9, 15, 8, 16), (2, 9, 31, 8, 16), (1, 7, 129, 8, 8), (1, 5, 1000, 8, 8), (1, 700, 3, 16, 8),
+    (2, 9, 48, 40, 24), (1, 3, 144, 8, 8), (1, 2, 256, 8, 40), (3, 65, 128, 8, 8), (1, 33, 272, 8, 8),
     (8, 33, 32, 64, 96),  # 8448 pixels: three chunks, each ends inside an image
     (32, 32, 32, 8, 32),  # eight chunks
 ])
@@ -86,7 +87,8 @@ def test_infinite_input_beside_the_padding(S, w):
     assert np.all(np.isfinite(db))
 
 
-@pytest.mark.parametrize("n,h,w,cin,cout", [(1, 1, 1, 8, 8), (3, 5, 7, 40, 24), (9, 31, 33, 32, 64)])
+@pytest.mark.parametrize("n,h,w,cin,cout", [(1, 1, 1, 8, 8), (3, 5, 7, 40, 24), (9, 31, 33, 32, 64), (2, 3, 16, 8, 40), (5, 33, 32, 32, 64),
+                                            (1, 9, 112, 8, 8), (3, 31, 128, 16, 32), (1, 3, 144, 8, 8)])
 def test_upconv_weight_gradient(S, n, h, w, cin, cout):
     import torch
     r = np.random.default_rng(h + w)
