@@ -209,26 +209,26 @@ __global__ __launch_bounds__(256) void igemm_fwd(GemmArgs a) {
 // outside the image) and the group's weights of its output channels in LDS
 // once, and all nine taps of all four waves read their MFMA fragments from
 // there.  Wave tile TM x TN MFMA tiles (32 x 32 each); the four waves are
-// stacked along the pixels, so a block covers 128 TM consecutive pixels --
+// stacked along the pixels, so a block covers 256 consecutive pixels --
 // whole image rows (16 <= w <= 256, w divides the block, h * w a multiple of
-// it) -- and 32 TN output channels.  Needs the reduction channels to be a
-// multiple of 16.
+// it) -- and 64 output channels.  Needs the reduction channels to be a
+// multiple of 16.  For images 16 columns wide and outputs that cannot be stored as
+// vectors; the rest goes to conv3x3_rows.
 // ---------------------------------------------------------------------------
-constexpr int conv_block_pix(int tm) { return 128 * tm; }
+constexpr int kConvBlockPix = 256;
 // largest staged region over the allowed widths: (pixels / w + 2) rows of w + 2
-constexpr int conv_halo_pix(int bp) {
+constexpr int conv_halo_pix() {
   int m = 0;
   for (int w = 16; w <= 256; w *= 2) {
-    const int v = (bp / w + 2) * (w + 2);
-    if (bp % w == 0 && v > m) m = v;
+    const int v = (kConvBlockPix / w + 2) * (w + 2);
+    m = v > m ? v : m;
   }
   return m;
 }
 
-template <int TM, int TN>
 __global__ __launch_bounds__(256) void conv3x3_lds(GemmArgs a) {
-  constexpr int BP = conv_block_pix(TM), BC = 32 * TN;
-  __shared__ uint4 sA[conv_halo_pix(BP) * 2];  // [region pixel][channel half of the group]
+  constexpr int TM = 2, TN = 2, BP = kConvBlockPix, BC = 32 * TN;
+  __shared__ uint4 sA[conv_halo_pix() * 2];  // [region pixel][channel half of the group]
   __shared__ uint4 sB[BC * 9 * 2];             // [output channel][tap][channel half]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5;
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void conv3x3_lds(GemmArgs a) {
   // loads go to registers before this group's taps run, and are parked in
   // LDS after the barrier that ends them.  Each thread's staged elements
   // keep their place from group to group; only the channel offset moves.
-  constexpr int KA = (conv_halo_pix(BP) * 2 + 255) / 256, KB = (BC * 9 * 2 + 255) / 256;
+  constexpr int KA = (conv_halo_pix() * 2 + 255) / 256, KB = (BC * 9 * 2 + 255) / 256;
   const int nA = rows * rw * 2;
   constexpr uint32_t kNone = 0xffffffffu;  // element outside the image or the weights
   uint32_t offA[KA], offB[KB];              // element offsets (host keeps them below 2^32 - 1)
@@ -331,8 +331,9 @@ __global__ __launch_bounds__(256) void conv3x3_lds(GemmArgs a) {
   }
 }
 
-// Can the LDS-staged kernel with block of bp pixels run this convolution?
-static bool conv_lds_fits(const GemmArgs &a, int bp) {
+// Can the LDS-staged kernel run this convolution?
+static bool conv_lds_fits(const GemmArgs &a) {
+  const int bp = kConvBlockPix;
   // element offsets of the input and the weights must fit 32 bits
   const bool small = (int64_t)a.n * a.h * a.w * a.x_cs < ((int64_t)1 << 32) - 1 &&
                      (int64_t)a.nout * 9 * a.kc < ((int64_t)1 << 32) - 1;
@@ -340,28 +341,46 @@ static bool conv_lds_fits(const GemmArgs &a, int bp) {
          ((int64_t)a.h * a.w) % bp == 0;
 }
 
+// Two floats rounded to BF16 (to nearest even, as f2bf; a NaN stays a quiet NaN).
+__device__ __forceinline__ uint32_t f2bf_pair(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
+  const floatx2 v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
 // Output of a transposed 32 x 32 product tile: this lane holds channels
-// c0 + 8 q + 4 half + 0..3 of pixel o in registers 4 q .. 4 q + 3.  Bias, ReLU and
-// rounding to BF16; then the lane halves trade registers, so that each stores
+// c0 + 8 q + 4 half + 0..3 of pixel o in registers 4 q .. 4 q + 3.  Bias (loaded
+// beforehand: a load between two tiles' stores would wait for the first's), ReLU
+// and rounding to BF16; then the lane halves trade registers, so that each stores
 // 16-byte runs of channels (channel counts, strides and offsets multiples of
-// 8, y 16-byte aligned).  bias: a buffer of the biases, empty for none.
-__device__ __forceinline__ void store_pixel(const GemmArgs &a, __amdgpu_buffer_rsrc_t bias, const floatx16 &acc, bool in,
+// 8, y 16-byte aligned).
+struct BiasRun {
+  float4 b[4];
+};
+// buffer: of the biases, empty for none
+__device__ __forceinline__ BiasRun load_bias(__amdgpu_buffer_rsrc_t buffer, int c0, int half) {
+  BiasRun r;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    r.b[q] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(buffer, 4 * (c0 + 8 * q + 4 * half), 0, 0));
+  return r;
+}
+
+__device__ __forceinline__ void store_pixel(const GemmArgs &a, const BiasRun &bias, const floatx16 &acc, bool in,
                                             int64_t o, int c0, int half) {
   uint32_t w[8];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const float4 b = __builtin_bit_cast(
-        float4, __builtin_amdgcn_raw_buffer_load_b128(bias, 4 * (c0 + 8 * q + 4 * half), 0, 0));
-    const float bv[4] = {b.x, b.y, b.z, b.w};
-    uint16_t h[4];
+    const float bv[4] = {bias.b[q].x, bias.b[q].y, bias.b[q].z, bias.b[q].w};
+    float v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      float v = acc[4 * q + k] + bv[k];
-      if (a.relu) v = v > 0.f ? v : 0.f;
-      h[k] = f2bf(v);
+      v[k] = acc[4 * q + k] + bv[k];
+      if (a.relu) v[k] = v[k] > 0.f ? v[k] : 0.f;
     }
-    w[2 * q] = h[0] | ((uint32_t)h[1] << 16);
-    w[2 * q + 1] = h[2] | ((uint32_t)h[3] << 16);
+    w[2 * q] = f2bf_pair(v[0], v[1]);
+    w[2 * q + 1] = f2bf_pair(v[2], v[3]);
   }
   // lower half: channels 0..7 and 16..23; upper half: 8..15 and 24..31
   uint16_t *const y = a.y + o * a.y_cs + a.y_co + c0;
@@ -462,6 +481,11 @@ __global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
   auto get = [](auto r, uint32_t off, int s) {
     return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, s, 0));
   };
+  const auto bias = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.bias), 0, a.bias ? 4 * a.nout : 0, 0x00027000);
+  constexpr int NB = ORDER == 3 ? 1 : TN;
+  BiasRun b[NB];
+#pragma unroll
+  for (int u = 0; u < NB; ++u) b[u] = load_bias(bias, col0 + 32 * u, half);
   floatx16 acc[TM][TN];
 #pragma unroll
   for (int t = 0; t < TM; ++t)
@@ -560,7 +584,6 @@ __global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
       if (s + i < steps) products(i);
   }
   // C[channel 8 (r / 4) + 4 half + r % 4][pixel l31]
-  const auto bias = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.bias), 0, a.bias ? 4 * a.nout : 0, 0x00027000);
 #pragma unroll
   for (int t = 0; t < TM; ++t) {
     const int64_t p = pix0 + 32 * t + l31;
@@ -572,9 +595,191 @@ __global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
         o = (2 * r + (u >> 1)) * W2 + 2 * (p - r * a.w) + (u & 1);
       }
       const int c0 = col0 + (ORDER == 3 ? 0 : 32 * u);
-      store_pixel(a, bias, acc[t][u], p < P, o, c0, half);
+      store_pixel(a, b[ORDER == 3 ? 0 : u], acc[t][u], p < P, o, c0, half);
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// 3x3 convolution through LDS.  The reduction runs over 16-channel groups, and
+// within a group over the nine taps: k = (group, tap, channel).  A block takes
+// tiles of 512 pixels (rows of min(w, 128) columns) by 32 TN output channels in
+// turn; per group it stages the tile's input with a one-pixel halo (zero outside
+// the image) and the group's weights.
+// Four waves multiply and four stage, one of each per SIMD: the staging waves fill
+// one of two buffers while the other is read, their loads two groups further on,
+// and go straight on to the next tile, so the products wait for one barrier a
+// group and nothing else.  A multiplying wave owns 32 columns by four rows; with eight
+// products per six fragment reads LDS stays below the matrix cores (four per
+// four: level with them).  LDS holds [channel half][pixel] and [tap][channel
+// half][output channel], so that fragment reads are runs of 512 bytes.  The
+// products are transposed, as in the kernel above, for 16-byte stores.
+// Tiles are dealt to the XCDs in contiguous ranges (blocks go round the XCDs): a
+// range's channel tiles and halos meet in one L2.
+// 64 -> 64 channels, 16 x 128 x 128: 43 us with blocks of four waves that stage and
+// multiply in turn (256 pixels), 31 us so; 32 -> 32, 16 x 256 x 256: 65 us and 34 us
+// (its bytes: 28 us).  256 -> 128, 16 x 64 x 64: 49 and 40 us, 28 us without the
+// loads: 32-byte pieces of a pixel are what staging is bound by.  Loading two
+// groups at a time, so that the pieces of a line follow each other, gained nothing.
+// ---------------------------------------------------------------------------
+constexpr int kConvThreads = 512;
+constexpr int kConvTilePix = 512;
+
+template <int TN>
+__global__ __launch_bounds__(kConvThreads, TN == 1 ? 4 : 2) void conv3x3_rows(GemmArgs a, int items) {
+  constexpr int TM = 4, BC = 32 * TN;
+  constexpr int kPix = (TM + 2) * 130;  // staged pixels, most for 128 columns
+  // strides that keep the two channel halves, and the 18 weight planes, of a
+  // staging wave's writes on different banks
+  constexpr int kPlane = (kPix * 16 + 127) / 256 * 256 + 128, kWPlane = BC * 16 + 16;
+  constexpr int kW = 2 * kPlane, kBuf = kW + 18 * kWPlane;
+  __shared__ __attribute__((aligned(16))) char smem[2 * kBuf + 16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = a.w, h = a.h;
+  const int tw = w < 128 ? w : 128, th = kConvTilePix / tw, rw = tw + 2;
+  const int ctiles = (a.nout + BC - 1) / BC, xtiles = w / tw, ytiles = (h + th - 1) / th;
+  const int groups = a.kc / 16;
+  // this block's tiles: every (grid / 8)-th of its XCD's range
+  const int xcd = blockIdx.x & 7, step = gridDim.x >> 3;
+  const int first = (int)((int64_t)items * xcd / 8) + (int)(blockIdx.x >> 3);
+  const int end = (int)((int64_t)items * (xcd + 1) / 8);
+  if (first >= end) return;
+  const int stages = ((end - first - 1) / step + 1) * groups;
+  struct Tile {
+    int col0, x0, y0, img;
+  };
+  auto tile_of = [&](int item) {
+    Tile t;
+    int q = item / ctiles;
+    t.col0 = (item - q * ctiles) * BC;
+    int r = q / xtiles;
+    t.x0 = (q - r * xtiles) * tw;
+    t.img = r / ytiles;
+    t.y0 = (r - t.img * ytiles) * th;
+    return t;
+  };
+
+  if (wave >= 4) {
+    const int t0 = tid - 256;
+    constexpr int KA = (kPix * 2 + 255) / 256, KB = (BC * 18 + 255) / 256;
+    const uint32_t cs2 = 2u * (uint32_t)a.x_cs;
+    // piece i: 8 channels of a staged pixel, row ay column ax of the tile's halo,
+    // or of one output channel's tap; past the last, a spare place
+    int ay[KA], ax[KA], la[KA], lb[KB], bco[KB];
+    uint32_t offa[KA], offb[KB];
+#pragma unroll
+    for (int i = 0; i < KA; ++i) {
+      const int e = t0 + 256 * i, q = e >> 1, hf = e & 1;
+      const bool in = q < (th + 2) * rw;
+      ay[i] = in ? q / rw - 1 : -(1 << 30);
+      ax[i] = q % rw - 1;
+      offa[i] = (uint32_t)((q / rw) * w + q % rw) * cs2 + 16u * hf;
+      la[i] = in ? hf * kPlane + q * 16 : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < KB; ++i) {
+      const int e = t0 + 256 * i, co = e / 18, rem = e - 18 * co;
+      bco[i] = e < BC * 18 ? co : 1 << 30;
+      offb[i] = 2u * (uint32_t)((co * 9 + (rem >> 1)) * a.kc) + 16u * (rem & 1);
+      lb[i] = e < BC * 18 ? kW + rem * kWPlane + co * 16 : -1;
+    }
+    struct Staged {
+      uint4 a[KA], b[KB];
+    } st[2];
+    int item = first, g = 0;  // of the next stage to load
+    auto load = [&](Staged &s) __attribute__((always_inline)) {
+      const Tile t = tile_of(item);
+      const uint16_t *const xp = a.x + a.x_co + (((int64_t)t.img * h + t.y0 - 1) * w + t.x0 - 1) * a.x_cs + 16 * g;
+      const uint16_t *const wp = a.wgt + (int64_t)t.col0 * 9 * a.kc + 16 * g;
+#pragma unroll
+      for (int i = 0; i < KA; ++i) {
+        const bool in = (unsigned)(t.y0 + ay[i]) < (unsigned)h && (unsigned)(t.x0 + ax[i]) < (unsigned)w;
+        s.a[i] = buffer_load16(xp, kWholeBuffer, in ? offa[i] : kOutside);
+      }
+#pragma unroll
+      for (int i = 0; i < KB; ++i) s.b[i] = buffer_load16(wp, kWholeBuffer, bco[i] < a.nout - t.col0 ? offb[i] : kOutside);
+      if (++g == groups) {  // past the last stage: the last tile again, not used
+        g = 0;
+        item = item + step < end ? item + step : item;
+      }
+    };
+    auto put = [&](int odd, const Staged &s) __attribute__((always_inline)) {
+      // (no branch may part these waits from the loads they count)
+#pragma unroll
+      for (int i = 0; i < KA; ++i)
+        *reinterpret_cast<uint4 *>(smem + (la[i] >= 0 ? la[i] + odd * kBuf : 2 * kBuf)) = s.a[i];
+#pragma unroll
+      for (int i = 0; i < KB; ++i)
+        *reinterpret_cast<uint4 *>(smem + (lb[i] >= 0 ? lb[i] + odd * kBuf : 2 * kBuf)) = s.b[i];
+    };
+    load(st[0]);
+    load(st[1]);
+    put(0, st[0]);
+    load(st[0]);
+    __syncthreads();
+    for (int i = 0; i < stages; i += 2) {
+      put(1, st[1]);
+      load(st[1]);
+      __syncthreads();
+      put(0, st[0]);
+      load(st[0]);
+      __syncthreads();
+    }
+    return;
+  }
+
+  const int half = lane >> 5, l31 = lane & 31;
+  const int strips = tw >> 5, row0 = wave / strips * TM, x = (wave % strips) * 32 + l31;
+  const auto bias = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.bias), 0, a.bias ? 4 * a.nout : 0, 0x00027000);
+  int arow[TM + 2];
+#pragma unroll
+  for (int r = 0; r < TM + 2; ++r) arow[r] = half * kPlane + ((row0 + r) * rw + x) * 16;
+  const int brow = kW + half * kWPlane + l31 * 16;
+  floatx16 acc[TM][TN] = {};
+  int item = first, g = 0;
+  __syncthreads();
+  for (int i = 0; i < stages; ++i) {
+    const int buf = (i & 1) * kBuf;
+    bf16x8 A[2][TM], B[2][TN];
+    auto fetch = [&](int tap) __attribute__((always_inline)) {
+      const int k = tap & 1, dy = tap / 3, dx = tap % 3;
+#pragma unroll
+      for (int u = 0; u < TN; ++u)
+        B[k][u] = *reinterpret_cast<const bf16x8 *>(smem + buf + brow + 2 * tap * kWPlane + 512 * u);
+#pragma unroll
+      for (int t = 0; t < TM; ++t) A[k][t] = *reinterpret_cast<const bf16x8 *>(smem + buf + arow[t + dy] + 16 * dx);
+    };
+    fetch(0);
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      if (tap < 8) fetch(tap + 1);
+      __builtin_amdgcn_sched_barrier(0);  // the fetches stay ahead of the products
+#pragma unroll
+      for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int u = 0; u < TN; ++u) acc[t][u] = mfma(B[tap & 1][u], A[tap & 1][t], acc[t][u]);
+    }
+    __syncthreads();
+    if (++g < groups) continue;
+    g = 0;
+    const Tile q = tile_of(item);
+    item += step;
+    BiasRun b[TN];
+#pragma unroll
+    for (int u = 0; u < TN; ++u) b[u] = load_bias(bias, q.col0 + 32 * u, half);
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      const int y = q.y0 + row0 + t;
+      const int64_t o = ((int64_t)q.img * h + y) * w + q.x0 + x;
+#pragma unroll
+      for (int u = 0; u < TN; ++u) {
+        store_pixel(a, b[u], acc[t][u], y < h, o, q.col0 + 32 * u, half);
+        acc[t][u] = floatx16{};
+      }
+    }
+  }
+  if (stages & 1) __syncthreads();  // the staging waves go in pairs
 }
 
 // The general kernel's launch: reduction channels not a multiple of 16 (8 has
@@ -591,11 +796,6 @@ static void launch_gather(const GemmArgs &a, int64_t P, int taps_z, hipStream_t 
   }
 }
 
-// Blocks of the staged convolution (of 64 channels) up to which the direct kernel
-// is faster: the staged one then leaves most CUs idle.  256 -> 128 channels on
-// 16 x 32 x 32 pixels (128 blocks): 54 us direct, 28 us staged.
-constexpr int64_t kDirectBlocks = 64;
-
 template <int ORDER, int TM, int TN, int GP = 1>
 static void launch_direct(const GemmArgs &a, int64_t P, hipStream_t s) {
   const int64_t pt = (P + 32 * TM - 1) / (32 * TM);
@@ -611,10 +811,15 @@ static void launch_direct(const GemmArgs &a, int64_t P, hipStream_t s) {
 template <int ORDER>
 static void launch_direct_tiles(const GemmArgs &a, int64_t P, hipStream_t s) {
   const int64_t t = ((P + 31) / 32) * ((a.nout + 31) / 32);  // 32 x 32 tiles
-  if (a.nout > 32 && t >= 4 * 1024) launch_direct<ORDER, 2, 2>(a, P, s);
-  else if (t >= 2 * 1024) launch_direct<ORDER, 2, 1>(a, P, s);
-  else if (ORDER == 0 && a.kc % 32 == 0) launch_direct<ORDER, 1, 1, ORDER == 0 ? 2 : 1>(a, P, s);
-  else launch_direct<ORDER, 1, 1>(a, P, s);
+  if constexpr (ORDER == 0) {  // (fewer tiles than 4096 come here)
+    if (t >= 2 * 1024) launch_direct<0, 2, 1>(a, P, s);
+    else if (a.kc % 32 == 0) launch_direct<0, 1, 1, 2>(a, P, s);
+    else launch_direct<0, 1, 1>(a, P, s);
+  } else {
+    if (a.nout > 32 && t >= 4 * 1024) launch_direct<ORDER, 2, 2>(a, P, s);
+    else if (t >= 2 * 1024) launch_direct<ORDER, 2, 1>(a, P, s);
+    else launch_direct<ORDER, 1, 1>(a, P, s);
+  }
 }
 
 // Can the direct kernel run this?  Its stores are vectors of 8 channels; the
@@ -627,23 +832,50 @@ static bool direct_fits(const GemmArgs &a, int64_t P, int taps) {
   return reach < kWholeBuffer && wbytes < ((int64_t)1 << 29) && ((P + 31) / 32) * ((a.nout + 31) / 32) < ((int64_t)1 << 31);
 }
 
+// Tiles of conv3x3_rows, and can it run this?
+static int64_t conv_rows_tiles(const GemmArgs &a, int bc) {
+  const int tw = a.w < 128 ? a.w : 128, th = kConvTilePix / tw;
+  return (int64_t)a.n * ((a.h + th - 1) / th) * (a.w / tw) * ((a.nout + bc - 1) / bc);
+}
+static bool conv_rows_fits(const GemmArgs &a, int64_t P) {
+  const int64_t rows = a.w < 128 ? kConvTilePix / a.w + 2 : kConvTilePix / 128 + 2;
+  return a.w >= 32 && conv_lds_fits(a) && direct_fits(a, P, 9) && rows * a.w * a.x_cs * 2 < kWholeBuffer;
+}
+
+template <int TN>
+static void launch_conv_rows(const GemmArgs &a, hipStream_t s) {
+  // one tile of 64 channels, two of 32 per CU at a time
+  const int64_t tiles = conv_rows_tiles(a, 32 * TN), most = TN == 1 ? 512 : 256;
+  conv3x3_rows<TN><<<dim3((unsigned)(tiles < most ? (tiles + 7) / 8 * 8 : most)), kConvThreads, 0, s>>>(a, (int)tiles);
+}
+
+// Group by group where the staged kernels can run (a rule on the shape alone: the
+// order of the sums may not change with the number of images), tap by tap elsewhere.
+// Within the first, by tiles of 512 pixels x 32 channels, us direct / through LDS:
+//   64 -> 32 at 1 x 128 x 128 (32 tiles) 6.5 / 9.5, at two images (64) 10.6 / 9.4;
+//   128 -> 128 at 1 x 64 x 64 (32) 10.3 / 12.8, at two (64) 18.5 / 13.0;
+//   32 -> 32 at 1 x 256 x 256 (128) 7.1 / 7.9, at two (256) 11.1 / 9.1.
+// 64-channel tiles once there is one per CU: 64 -> 64 at 4 x 128 x 128 13.9 (13.1
+// with 32), at eight images 18.7 (21.5).
 static void launch_conv3x3(const GemmArgs &a, int64_t P, hipStream_t s) {
   const bool direct = direct_fits(a, P, 9);
   if (direct && a.kc == 8) {
     if (P >= 2 * 32 * 1024) launch_direct<2, 2, 1>(a, P, s);
     else launch_direct<2, 1, 1>(a, P, s);
-    return;
+  } else if (conv_rows_fits(a, P) && conv_rows_tiles(a, 32) >= (a.kc > 32 ? 64 : 192)) {
+    if (a.nout > 32 && conv_rows_tiles(a, 64) >= 256) launch_conv_rows<2>(a, s);
+    else launch_conv_rows<1>(a, s);
+  } else if (conv_lds_fits(a)) {
+    // sixteen columns wide, or too few tiles, or outputs that are not whole
+    // vectors: 64 blocks of the staged kernel leave most CUs idle
+    const dim3 g((unsigned)(P / kConvBlockPix), (unsigned)((a.nout + 63) / 64));
+    if (direct && (a.w >= 32 || (int64_t)g.x * g.y <= 64)) launch_direct_tiles<0>(a, P, s);
+    else conv3x3_lds<<<g, 256, 0, s>>>(a);
+  } else if (direct && a.kc % 16 == 0) {
+    launch_direct_tiles<1>(a, P, s);
+  } else {
+    launch_gather<0>(a, P, 1, s);
   }
-  const int tm = a.nout <= 32 && conv_lds_fits(a, conv_block_pix(4)) ? 4 : 2;
-  if (conv_lds_fits(a, conv_block_pix(tm))) {
-    const dim3 g((unsigned)(P / conv_block_pix(tm)), tm == 4 ? 1u : (unsigned)((a.nout + 63) / 64));
-    if (direct && (int64_t)g.x * g.y <= (tm == 4 ? 2 * kDirectBlocks : kDirectBlocks)) launch_direct_tiles<0>(a, P, s);
-    else if (tm == 4) conv3x3_lds<4, 1><<<g, 256, 0, s>>>(a);
-    else conv3x3_lds<2, 2><<<g, 256, 0, s>>>(a);
-    return;
-  }
-  if (direct && a.kc % 16 == 0) launch_direct_tiles<1>(a, P, s);
-  else launch_gather<0>(a, P, 1, s);
 }
 
 // ---------------------------------------------------------------------------

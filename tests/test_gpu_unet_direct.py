@@ -1,8 +1,8 @@
-"""Convolutions whose waves read their operands straight from memory, at the
-sizes where their tiles, slices and fallbacks meet: remainders of 32- and
-64-pixel tiles, of 32- and 64-channel tiles and of the four-wave blocks, one-row
-and one-column images, channel slices on both sides, and outputs that take the
-general kernel (channels or offsets that are not whole vectors of eight).
+"""Convolutions at the sizes where their kernels' tiles, slices and fallbacks
+meet: remainders of 32- and 64-pixel tiles, of 32- and 64-channel tiles and of
+the four-wave blocks, one-row and one-column images, channel slices on both
+sides, more tiles than blocks, and outputs that take the general kernel (channels
+or offsets that are not whole vectors of eight).
 Bound: BF16 products are exact and summed in FP32 (1e-5 of the sum of |terms|,
 fewer than 2^12 terms), then rounded to BF16 once (2^-8 of the value)."""
 import numpy as np
@@ -57,6 +57,12 @@ def _check(S, y, co, cout, ref, terms):
     # 16-channel groups outermost (whole rows per 256 or 512 pixels)
     (1, 16, 16, 16, 8, 16, 0, 8, 0), (1, 16, 16, 48, 96, 56, 8, 104, 8), (1, 8, 32, 64, 40, 64, 0, 40, 0),
     (3, 4, 128, 32, 24, 32, 0, 32, 8), (2, 256, 128, 16, 24, 16, 0, 24, 0),
+    # the same through LDS, in tiles of 512 pixels: last tiles that are not whole, one and an odd
+    # number of groups, more tiles than blocks, 64-channel tiles with 32 or fewer in the last
+    (33, 24, 32, 48, 8, 48, 0, 8, 0), (8, 12, 64, 64, 104, 72, 8, 120, 8), (33, 2, 128, 48, 40, 48, 0, 40, 0),
+    (17, 63, 256, 16, 24, 24, 8, 32, 8), (4, 65, 256, 32, 72, 32, 0, 72, 0), (9, 65, 256, 48, 40, 48, 0, 40, 0),
+    # sixteen columns, staged 256 pixels at a time
+    (70, 16, 16, 16, 40, 16, 0, 40, 0),
     # input layer
     (1, 1, 1, 8, 8, 8, 0, 8, 0), (2, 9, 13, 8, 40, 24, 8, 48, 8), (1, 257, 259, 8, 72, 8, 0, 72, 0),
     # general kernel: partial groups, outputs that are not whole vectors
