@@ -1487,29 +1487,70 @@ __device__ __forceinline__ float strided_sum(const float *p, int64_t count, int6
   return ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
 }
 
-// dw[m][tap][n] (+)= sum over kblocks of partial[kb][tap][m][n], fixed order.
-// For MODE 0 ntap = 1 and n = (tap, ci) already.
-__global__ void wgrad_reduce(const float *partial, int kblocks, int ntap, int cout, int ncol, float *dw,
-                             int accumulate) {
+// Weight and bias gradients from the partial sums, in one launch:
+//   dw[m][tap][n] (+)= sum over kblocks of partial[kb][tap][m][n]
+//     (MODE 0: ntap = 1 and n = (tap, ci) already),
+//   db[c] (+)= sum over the bparts bias partials, by the last ceil(cout / 32) blocks.
+// The sums are strided_sum's.  SPLIT: eight threads share an element, one per partial
+// sum, so that the few elements of the wide layers (9216 by 256 partials) have
+// enough loads in flight: 5 us, with a thread per element and a launch for the
+// biases 13.5 and 9.8 us.
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void wgrad_reduce(const float *partial, int kblocks, int ntap, int cout, int ncol,
+                                                    float *dw, int accumulate, int wblocks, const float *bpartial,
+                                                    int64_t bparts, float *db) {
   const int64_t total = (int64_t)ntap * cout * ncol;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int tap = (int)(e / ((int64_t)cout * ncol));
-    const int64_t rem = e - (int64_t)tap * cout * ncol;
-    const int m = (int)(rem / ncol), n = (int)(rem - (int64_t)m * ncol);
-    const float s = strided_sum(partial + e, kblocks, total);
-    const int64_t o = ((int64_t)m * ntap + tap) * ncol + n;  // [co][tap][ci]
-    dw[o] = accumulate ? dw[o] + s : s;
+  const int tid = threadIdx.x;
+  const bool bias = blockIdx.x >= (unsigned)wblocks;
+  float s;
+  int64_t e;
+  if (SPLIT || bias) {
+    __shared__ float part[8][33];
+    const int j = tid >> 5, i = tid & 31;
+    e = (bias ? blockIdx.x - wblocks : blockIdx.x) * (int64_t)32 + i;
+    const float *const p = bias ? bpartial : partial;
+    const int64_t count = bias ? bparts : kblocks, stride = bias ? cout : total;
+    float v = 0.f;
+    if (e < stride) {
+      int64_t k = j;
+      for (; k + 24 < count; k += 32) {
+        float u[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = p[(k + 8 * q) * stride + e];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v += u[q];
+      }
+      for (; k < count; k += 8) v += p[k * stride + e];
+    }
+    part[j][i] = v;
+    __syncthreads();
+    if (tid >= 32 || e >= stride) return;
+    s = ((part[0][i] + part[1][i]) + (part[2][i] + part[3][i])) + ((part[4][i] + part[5][i]) + (part[6][i] + part[7][i]));
+  } else {
+    e = blockIdx.x * (int64_t)256 + tid;
+    if (e >= total) return;
+    s = strided_sum(partial + e, kblocks, total);
   }
+  if (bias) {
+    db[e] = accumulate ? db[e] + s : s;
+    return;
+  }
+  const int tap = (int)(e / ((int64_t)cout * ncol));
+  const int64_t rem = e - (int64_t)tap * cout * ncol;
+  const int m = (int)(rem / ncol), n = (int)(rem - (int64_t)m * ncol);
+  const int64_t o = ((int64_t)m * ntap + tap) * ncol + n;  // [co][tap][ci]
+  dw[o] = accumulate ? dw[o] + s : s;
 }
 
-// db[c] (+)= sum over the weight-gradient blocks' bias partials, fixed order.
-__global__ void bias_reduce(const float *bpartial, int64_t nparts, int c, float *db, int accumulate) {
-  const int ch = blockIdx.x * blockDim.x + threadIdx.x;
-  if (ch >= c) return;
-  const float s = strided_sum(bpartial + ch, nparts, c);
-  db[ch] = accumulate ? db[ch] + s : s;
+static void launch_wgrad_reduce(const float *partial, int kb, int ntap, int cout, int ncol, float *dw, int accumulate,
+                                const float *bpartial, int64_t bparts, float *db, hipStream_t s) {
+  const int64_t total = (int64_t)ntap * cout * ncol;
+  const bool split = kb >= 32;  // (fewer partials are in flight at once anyway)
+  const int wblocks = (int)((total + (split ? 31 : 255)) / (split ? 32 : 256));
+  const int blocks = wblocks + (db ? (cout + 31) / 32 : 0);
+  if (split) wgrad_reduce<true><<<blocks, 256, 0, s>>>(partial, kb, ntap, cout, ncol, dw, accumulate, wblocks, bpartial, bparts, db);
+  else wgrad_reduce<false><<<blocks, 256, 0, s>>>(partial, kb, ntap, cout, ncol, dw, accumulate, wblocks, bpartial, bparts, db);
 }
-
 
 // wt[ci][ky][kx][co] = w[co][2-ky][2-kx][ci]
 __global__ void conv_flip(const uint16_t *w, int cout, int cin, uint16_t *wt) {
@@ -1561,6 +1602,98 @@ __global__ void maxpool_fwd_kernel(const uint16_t *x, int n, int h, int w, int c
         if (bf2f(v) > m) { m = bf2f(v); best = v; }
       }
     y[q * y_cs + y_co + ch] = best;
+  }
+}
+
+// Pooling by vectors of eight channels, a window's eight channels per thread (channel
+// counts, strides and offsets multiples of 8, fewer than 2^31 vectors).  Bound by
+// memory: 16 x 256 x 256 x 32 in a slice of 64 channels, forward 27 us (37 us with a
+// channel per thread); backward 64 us both ways, at 64 x 64 x 128 13 us (20 us).
+struct Window {
+  int64_t p;  // its first pixel
+  int64_t q;  // its pixel of the half-size grid
+  int ch;
+};
+__device__ __forceinline__ Window pool_window(unsigned e, unsigned w2, unsigned c8, int w) {
+  const unsigned q = e / c8, row = q / w2;  // rows are linear over images on both grids
+  return {(int64_t)row * 2 * w + 2 * (int64_t)(q - row * w2), (int64_t)q, (int)(e - q * c8) * 8};
+}
+__device__ __forceinline__ void unpack8(const uint4 &v, uint16_t (&o)[8]) {
+  const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    o[2 * k] = (uint16_t)(u[k] & 0xffffu);
+    o[2 * k + 1] = (uint16_t)(u[k] >> 16);
+  }
+}
+
+__global__ __launch_bounds__(256) void maxpool_fwd_vec(const uint16_t *x, unsigned total, int w, int c8, int x_cs,
+                                                       int x_co, uint16_t *y, int y_cs, int y_co) {
+  const unsigned e = blockIdx.x * 256u + threadIdx.x;
+  if (e >= total) return;
+  const Window o = pool_window(e, (unsigned)w / 2, (unsigned)c8, w);
+  const uint16_t *const px = x + o.p * x_cs + x_co + o.ch;
+  uint4 v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const uint4 *>(px + (int64_t)((k >> 1) * w + (k & 1)) * x_cs);
+  uint16_t best[8] = {};
+  float m[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) m[j] = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint16_t t[8];
+    unpack8(v[k], t);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (bf2f(t[j]) > m[j]) {
+        m[j] = bf2f(t[j]);
+        best[j] = t[j];
+      }
+  }
+  *reinterpret_cast<bf16x8 *>(y + o.q * y_cs + y_co + o.ch) = pack8(best);
+}
+
+__global__ __launch_bounds__(256) void maxpool_bwd_vec(const uint16_t *x, unsigned total, int w, int c8, int x_cs,
+                                                       int x_co, const uint16_t *dy, int dy_cs, int dy_co, uint16_t *dx,
+                                                       int dx_cs, int dx_co, int accumulate) {
+  const unsigned e = blockIdx.x * 256u + threadIdx.x;
+  if (e >= total) return;
+  const Window o = pool_window(e, (unsigned)w / 2, (unsigned)c8, w);
+  const uint16_t *const px = x + o.p * x_cs + x_co + o.ch;
+  uint16_t *const pd = dx + o.p * dx_cs + dx_co + o.ch;
+  uint4 v[4], d[4] = {};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const uint4 *>(px + (int64_t)((k >> 1) * w + (k & 1)) * x_cs);
+  uint16_t g[8];
+  unpack8(*reinterpret_cast<const uint4 *>(dy + o.q * dy_cs + dy_co + o.ch), g);
+  if (accumulate) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) d[k] = *reinterpret_cast<const uint4 *>(pd + (int64_t)((k >> 1) * w + (k & 1)) * dx_cs);
+  }
+  float m[8];
+  int arg[8] = {};
+#pragma unroll
+  for (int j = 0; j < 8; ++j) m[j] = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint16_t t[8];
+    unpack8(v[k], t);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (bf2f(t[j]) > m[j]) {
+        m[j] = bf2f(t[j]);
+        arg[j] = k;
+      }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint16_t t[8];
+    unpack8(d[k], t);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (k == arg[j]) t[j] = accumulate ? f2bf(bf2f(t[j]) + bf2f(g[j])) : g[j];
+    *reinterpret_cast<bf16x8 *>(pd + (int64_t)((k >> 1) * w + (k & 1)) * dx_cs) = pack8(t);
   }
 }
 
@@ -1667,6 +1800,60 @@ __global__ void head_loss_pix(const uint16_t *x, int64_t n_pix, int c, int x_cs,
   }
 }
 
+// The same by vectors (c a power of two from 8 to 64, x_cs a multiple of 8, x and dx
+// 16-byte aligned): 256 pixels pass through LDS, so that global accesses are runs of
+// whole pixels while a thread still adds up one pixel's channels in order.  Bound by
+// memory: 16 x 256 x 256 pixels of 32 channels 34 us (71 us with a pixel per thread).
+__global__ __launch_bounds__(256) void head_loss_pix_v(const uint16_t *x, int64_t n_pix, int c, int x_cs,
+                                                       const float *w, const float *b, const float *t,
+                                                       const uint8_t *mask, float scale, uint16_t *dx, float *g_out,
+                                                       float *l_out) {
+  __shared__ __attribute__((aligned(16))) char sx[256 * (64 * 2 + 16)];
+  __shared__ float sw[64], sg[256];
+  const int tid = threadIdx.x, c8 = c / 8, pitch = 2 * c + 16;  // (the odd 16 bytes spread pixels over the banks)
+  const int64_t p0 = blockIdx.x * (int64_t)256;
+  if (tid < c) sw[tid] = w[tid];
+  for (int e = tid; e < 256 * c8; e += 256) {
+    const int q = e / c8, k = e - q * c8;
+    if (p0 + q < n_pix)
+      *reinterpret_cast<uint4 *>(sx + q * pitch + 16 * k) = *reinterpret_cast<const uint4 *>(x + (p0 + q) * x_cs + 8 * k);
+  }
+  __syncthreads();
+  const int64_t p = p0 + tid;
+  if (p < n_pix) {
+    float z = b[0];
+    for (int k = 0; k < c8; ++k) {
+      uint16_t v[8];
+      const uint4 q = *reinterpret_cast<const uint4 *>(sx + tid * pitch + 16 * k);
+      const uint32_t u[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[2 * j] = (uint16_t)(u[j] & 0xffffu);
+        v[2 * j + 1] = (uint16_t)(u[j] >> 16);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) z += sw[8 * k + j] * bf2f(v[j]);
+    }
+    const bool on = mask[p] != 0;
+    const float sp = fmaxf(z, 0.f) + log1pf(__expf(-fabsf(z)));
+    const float s = 1.f / (1.f + __expf(-z));
+    const float g = on ? (s - t[p]) * scale : 0.f;
+    g_out[p] = g;
+    l_out[p] = on ? (sp - t[p] * z) * scale : 0.f;
+    sg[tid] = g;
+  }
+  if (!dx) return;
+  __syncthreads();
+  for (int e = tid; e < 256 * c8; e += 256) {
+    const int q = e / c8, k = e - q * c8;
+    if (p0 + q >= n_pix) break;
+    uint32_t u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u[j] = f2bf_pair(sg[q] * sw[8 * k + 2 * j], sg[q] * sw[8 * k + 2 * j + 1]);
+    *reinterpret_cast<uint4 *>(dx + (p0 + q) * c + 8 * k) = make_uint4(u[0], u[1], u[2], u[3]);
+  }
+}
+
 // Block partials over a pixel chunk: threads = (256 / c) pixel lanes x c
 // channels.  out[block] = {sum l, sum g, sum g x[.][0..c)}.
 constexpr int kHeadPix = 4096;
@@ -1713,19 +1900,32 @@ __global__ void head_loss_sums_v(const uint16_t *x, int64_t n_pix, int c, int x_
   const int64_t p0 = (int64_t)blockIdx.x * kHeadPix;
   float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float sl = 0.f, sg = 0.f;
-  for (int k = pl; k < kHeadPix; k += lanes) {
-    const int64_t p = p0 + k;
-    if (p >= n_pix) break;
-    const float gv = g[p];
-    const uint4 v = *reinterpret_cast<const uint4 *>(x + p * x_cs + cg * 8);
+  // whole chunks: eight pixels' loads in flight (15 us for 16 x 256 x 256 pixels of 32
+  // channels; one at a time 34 us)
+  const int64_t end = p0 + kHeadPix < n_pix ? p0 + kHeadPix : n_pix;
+  int64_t p = p0 + pl;
+  auto add = [&](float gv, float lv, const uint4 &v) {
     const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       a[2 * q] += gv * bf2f((uint16_t)(u[q] & 0xffffu));
       a[2 * q + 1] += gv * bf2f((uint16_t)(u[q] >> 16));
     }
-    if (cg == 0) { sl += l[p]; sg += gv; }
+    if (cg == 0) { sl += lv; sg += gv; }
+  };
+  for (; p + 7 * lanes < end; p += 8 * lanes) {
+    float gv[8], lv[8];
+    uint4 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      gv[i] = g[p + i * lanes];
+      lv[i] = l[p + i * lanes];
+      v[i] = *reinterpret_cast<const uint4 *>(x + (p + i * lanes) * x_cs + cg * 8);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) add(gv[i], lv[i], v[i]);
   }
+  for (; p < end; p += lanes) add(g[p], l[p], *reinterpret_cast<const uint4 *>(x + p * x_cs + cg * 8));
 #pragma unroll
   for (int j = 0; j < 8; ++j) red[threadIdx.x * 8 + j] = a[j];
   red_l[threadIdx.x] = sl;
@@ -1745,10 +1945,19 @@ __global__ void head_loss_sums_v(const uint16_t *x, int64_t n_pix, int c, int x_
   }
 }
 
-__global__ void head_loss_final(const float *partial, int blocks, int c, float *loss, float *dw, float *db) {
-  const int k = threadIdx.x;
-  if (k >= 2 + c) return;
-  const float s = strided_sum(partial + k, blocks, 2 + c);
+// (eight threads per sum, one per partial of strided_sum's order)
+__global__ __launch_bounds__(256) void head_loss_final(const float *partial, int blocks, int c, float *loss, float *dw,
+                                                       float *db) {
+  __shared__ float part[8][33];
+  const int j = threadIdx.x >> 5, i = threadIdx.x & 31, k = blockIdx.x * 32 + i;
+  float v = 0.f;
+  if (k < 2 + c)
+    for (int q = j; q < blocks; q += 8) v += partial[(int64_t)q * (2 + c) + k];
+  part[j][i] = v;
+  __syncthreads();
+  if (threadIdx.x >= 32 || k >= 2 + c) return;
+  const float s =
+      ((part[0][i] + part[1][i]) + (part[2][i] + part[3][i])) + ((part[4][i] + part[5][i]) + (part[6][i] + part[7][i]));
   if (k == 0) loss[0] = s;
   else if (k == 1) { if (db) db[0] = s; }
   else if (dw) dw[k - 2] = s;
@@ -1783,6 +1992,10 @@ static int grid1d(int64_t n) {
 }
 static int launched() { return hipGetLastError() == hipSuccess ? 0 : -100; }
 static bool ok8(int v) { return v > 0 && v % 8 == 0; }
+// channels co .. co + c of a pixel are whole aligned vectors of eight
+static bool vec8(const uint16_t *p, int c, int cs, int co) {
+  return reinterpret_cast<uintptr_t>(p) % 16 == 0 && c % 8 == 0 && cs % 8 == 0 && co % 8 == 0;
+}
 
 }  // namespace unet
 
@@ -1856,9 +2069,7 @@ int unet_conv3x3_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, 9 * cin, db ? partial + wpart : nullptr};
   if (wgrad_rows_fits(a, 256)) launch_wgrad_rows<0, 256>(a, kb, (hipStream_t)s);
   else launch_wgrad_taps<0>(a, kb, (hipStream_t)s);
-  wgrad_reduce<<<grid1d((int64_t)cout * 9 * cin), 256, 0, (hipStream_t)s>>>(partial, kb, 1, cout, 9 * cin, dw,
-                                                                             accumulate);
-  if (db) bias_reduce<<<(cout + 63) / 64, 64, 0, (hipStream_t)s>>>(partial + wpart, kb, cout, db, accumulate);
+  launch_wgrad_reduce(partial, kb, 1, cout, 9 * cin, dw, accumulate, partial + wpart, kb, db, (hipStream_t)s);
   return launched();
 }
 
@@ -1891,7 +2102,12 @@ int unet_maxpool_fwd(const uint16_t *x, int n, int h, int w, int c, int x_cs, in
   if (!x || !y || n < 1 || h < 2 || w < 2 || (h & 1) || (w & 1) || !slice_ok(x_co, c, x_cs) ||
       !slice_ok(y_co, c, y_cs))
     return -1;
-  maxpool_fwd_kernel<<<grid1d((int64_t)n * h * w * c / 4), 256, 0, (hipStream_t)s>>>(x, n, h, w, c, x_cs, x_co, y,
+  const int64_t vectors = (int64_t)n * h * w * c / 32;
+  if (vec8(x, c, x_cs, x_co) && vec8(y, c, y_cs, y_co) && vectors < ((int64_t)1 << 31))
+    maxpool_fwd_vec<<<(unsigned)((vectors + 255) / 256), 256, 0, (hipStream_t)s>>>(x, (unsigned)vectors, w, c / 8, x_cs,
+                                                                                   x_co, y, y_cs, y_co);
+  else
+    maxpool_fwd_kernel<<<grid1d((int64_t)n * h * w * c / 4), 256, 0, (hipStream_t)s>>>(x, n, h, w, c, x_cs, x_co, y,
                                                                                        y_cs, y_co);
   return launched();
 }
@@ -1901,8 +2117,13 @@ int unet_maxpool_bwd(const uint16_t *x, int n, int h, int w, int c, int x_cs, in
   if (!x || !dy || !dx || n < 1 || h < 2 || w < 2 || (h & 1) || (w & 1) || !slice_ok(x_co, c, x_cs) ||
       !slice_ok(dy_co, c, dy_cs) || !slice_ok(dx_co, c, dx_cs))
     return -1;
-  maxpool_bwd_kernel<<<grid1d((int64_t)n * h * w * c / 4), 256, 0, (hipStream_t)s>>>(
-      x, n, h, w, c, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate);
+  const int64_t vectors = (int64_t)n * h * w * c / 32;
+  if (vec8(x, c, x_cs, x_co) && vec8(dy, c, dy_cs, dy_co) && vec8(dx, c, dx_cs, dx_co) && vectors < ((int64_t)1 << 31))
+    maxpool_bwd_vec<<<(unsigned)((vectors + 255) / 256), 256, 0, (hipStream_t)s>>>(
+        x, (unsigned)vectors, w, c / 8, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate);
+  else
+    maxpool_bwd_kernel<<<grid1d((int64_t)n * h * w * c / 4), 256, 0, (hipStream_t)s>>>(
+        x, n, h, w, c, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate);
   return launched();
 }
 
@@ -1946,8 +2167,7 @@ int unet_upconv_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs,
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, cin, db ? partial + wpart : nullptr};
   if (wgrad_rows_fits(a, 128)) launch_wgrad_rows<1, 128>(a, kb, (hipStream_t)s);
   else launch_wgrad_taps<1>(a, kb, (hipStream_t)s);
-  wgrad_reduce<<<grid1d((int64_t)4 * cout * cin), 256, 0, (hipStream_t)s>>>(partial, kb, 4, cout, cin, dw, 0);
-  if (db) bias_reduce<<<(cout + 63) / 64, 64, 0, (hipStream_t)s>>>(partial + wpart, (int64_t)kb * 4, cout, db, 0);
+  launch_wgrad_reduce(partial, kb, 4, cout, cin, dw, 0, partial + wpart, (int64_t)kb * 4, db, (hipStream_t)s);
   return launched();
 }
 
@@ -1971,12 +2191,16 @@ int unet_head_loss_bwd(const uint16_t *x, int n_pix, int c, int x_cs, const floa
     return -1;
   float *g = partial, *l = partial + n_pix, *sums = partial + 2 * (int64_t)n_pix;
   const int blocks = (int)(((int64_t)n_pix + kHeadPix - 1) / kHeadPix);
-  head_loss_pix<<<grid1d(n_pix), 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, w, b, target, mask, scale, dx, g, l);
+  if (c <= 64 && vec8(x, c, x_cs, 0) && (!dx || vec8(dx, c, c, 0)))
+    head_loss_pix_v<<<(n_pix + 255) / 256, 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, w, b, target, mask, scale, dx, g,
+                                                                     l);
+  else
+    head_loss_pix<<<grid1d(n_pix), 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, w, b, target, mask, scale, dx, g, l);
   if ((c & 7) == 0 && (x_cs & 7) == 0)
     head_loss_sums_v<<<blocks, 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, g, l, sums);
   else
     head_loss_sums<<<blocks, 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, g, l, sums);
-  head_loss_final<<<1, 512, 0, (hipStream_t)s>>>(sums, blocks, c, loss, dw, db);
+  head_loss_final<<<(2 + c + 31) / 32, 256, 0, (hipStream_t)s>>>(sums, blocks, c, loss, dw, db);
   return launched();
 }
 

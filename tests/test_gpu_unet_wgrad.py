@@ -56,6 +56,7 @@ def _conv_wgrad(S, x, dy):
     (2, 9, 48, 40, 24), (1, 3, 144, 8, 8), (1, 2, 256, 8, 40), (3, 65, 128, 8, 8), (1, 33, 272, 8, 8),
     (8, 33, 32, 64, 96),  # 8448 pixels: three chunks, each ends inside an image
     (32, 32, 32, 8, 32),  # eight chunks
+    (2, 260, 256, 8, 16), (3, 211, 212, 8, 40),  # 33 chunks: eight threads to a sum
 ])
 def test_conv_weight_gradient(S, n, h, w, cin, cout):
     r = np.random.default_rng(h * w + cin)
