@@ -667,7 +667,10 @@ lbm_status create_batch(int32_t k, const lbm_geometry *g, const lbm_params *p,
   // not fit the L2), the fused step otherwise
   int strategy = resolve_strategy(g[0], p[0]);
   b->compact = compact_strategy(strategy);
-  const lbm_status ps = apply_plan(b, strategy, p[0].tile_rows ? p[0].tile_rows : fused_rows(b->storage, b->compact));
+  int64_t tiles = 0;
+  for (int i = 0; i < k; ++i) tiles += (int64_t)((g[i].nx + kTileX - 1) / kTileX) * ((g[i].ny + 7) / 8);
+  const lbm_status ps =
+      apply_plan(b, strategy, p[0].tile_rows ? p[0].tile_rows : fused_rows(b->storage, b->compact, tiles));
   if (ps != LBM_OK) return ps;
   *out = owner.release();
   return LBM_OK;

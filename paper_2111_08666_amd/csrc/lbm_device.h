@@ -24,10 +24,15 @@ constexpr int kTileX = 60;
 constexpr int fused_waves(int ty, bool f64, int storage, bool compact) {
   return ty == 8 && !(compact && !(f64 && storage == LBM_STORE_F32)) ? 8 : 4;
 }
-// Tile height of the fused D2Q9 step when none is asked for: 8 rows, but 12
-// on the compacted layout with BF16 storage, whose pulls are the dearest per
-// halo row (24 uneven instances: 109 us per step against 114 with 8).
-constexpr int fused_rows(int storage, bool compact) { return compact && storage != LBM_STORE_F32 ? 12 : 8; }
+// Tile height of the fused D2Q9 step when none is asked for (tiles: of 60 x 8 nodes,
+// all instances).  8 rows, but 12 with BF16 storage, whose pulls are the dearest
+// per halo row, where waves are not what is short: on the compacted layout (24
+// uneven instances: 109 us per step against 114 with 8), and on the dense one above
+// five tiles per CU (2648 tiles: 43 us against 47 with 8; 1472: 28 and 30;
+// 1064: 27 and 24; 24: 23 and 8.5).
+constexpr int fused_rows(int storage, bool compact, int64_t tiles) {
+  return storage != LBM_STORE_F32 && (compact || tiles > 1280) ? 12 : 8;
+}
 // 3D step tile: the same 64-lane rows, TY3 interior rows in y, marching in z.
 constexpr int kTileY3 = 8;
 // Compacted 3D fused step: a tile is one row word (64 columns) by kFwdRows

@@ -46,3 +46,18 @@ def test_default_tile_matches_the_four_wave_tile(lbm, ny, periodic, compact, sto
     a.step_graph(4, 3)  # replays, with the eager work above in between
     b.step(12)
     np.testing.assert_array_equal(a.density(), b.density())
+
+
+@pytest.mark.parametrize("ny,rows", [(5120, 8), (5121, 12)])
+def test_default_tile_of_many_tiles_with_bf16_storage(lbm, ny, rows):
+    """1280 tiles of 60 x 8 nodes take 8 rows, more take 12: the same densities."""
+    m = np.zeros((ny, 61), np.uint8)
+    m[ny // 2, 20:30] = 1
+    p = I.Problem(q=9, mask=m, rho0=I.tanh_droplet(m.shape, (30, ny / 2), 9, (1.0, 0.027), (0.027, 1.0), mask=m),
+                  periodic=3, open_x=0, tau=I.TAU_M10, G=3.5, xi=-0.3, collision=1)
+    kw = dict(strategy=lbm.FUSED, storage=1)
+    a, b = lbm.Solver(p, **kw), lbm.Solver(p, tile_rows=16, **kw)
+    assert a.kernel_info()[0].endswith(",%d>" % rows)
+    a.step(6)
+    b.step(6)
+    np.testing.assert_array_equal(a.density(), b.density())
