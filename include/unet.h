@@ -84,6 +84,29 @@ int unet_conv3x3_wgrad_noalloc(const uint16_t *x, int n, int h, int w, int cin, 
 int unet_relu_bwd(const uint16_t *y, int n_pix, int c, int y_cs, int y_co,
                   uint16_t *dy, int dy_cs, int dy_co, void *s);
 
+/* Data gradients whose ReLU backward is done as they are written (the result of
+ * the call without it followed by unet_relu_bwd):
+ *   unet_conv3x3_relu_bwd_data    dx = 3x3 data gradient of dy (wt: the weights
+ *     of unet_conv3x3_flip), zero where act, of dx's grid and channels, is not
+ *     positive;
+ *   unet_upconv_relu_bwd_data     unet_upconv_bwd_data, likewise;
+ *   unet_maxpool_relu_bwd         unet_maxpool_bwd, zero where x is not positive;
+ *   unet_head_loss_relu_bwd       unet_head_loss_bwd, dx zero where x is not
+ *     positive. */
+int unet_conv3x3_relu_bwd_data(const uint16_t *dy, int n, int h, int w, int cout, int dy_cs, int dy_co,
+                               const uint16_t *wt, int cin, uint16_t *dx, int dx_cs, int dx_co,
+                               const uint16_t *act, int act_cs, int act_co, void *s);
+int unet_upconv_relu_bwd_data(const uint16_t *dy, int n, int h, int w, int cout, int dy_cs, int dy_co,
+                              const uint16_t *wgt, int cin, uint16_t *wt,
+                              uint16_t *dx, int dx_cs, int dx_co,
+                              const uint16_t *act, int act_cs, int act_co, void *s);
+int unet_maxpool_relu_bwd(const uint16_t *x, int n, int h, int w, int c, int x_cs, int x_co,
+                          const uint16_t *dy, int dy_cs, int dy_co, uint16_t *dx, int dx_cs, int dx_co,
+                          int accumulate, void *s);
+int unet_head_loss_relu_bwd(const uint16_t *x, int n_pix, int c, int x_cs, const float *w, const float *b,
+                            const float *target, const uint8_t *mask, float scale, float *loss,
+                            uint16_t *dx, float *dw, float *db, float *partial, void *s);
+
 /* 2x2 max pooling with stride 2 (h, w even): y is n x h/2 x w/2.  Backward
  * recomputes the argmax from x (ties: first in (dy, dx) raster order) and
  * routes dy there; accumulate = 0 writes every element of the 2x2 window

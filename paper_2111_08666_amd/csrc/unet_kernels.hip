@@ -101,6 +101,10 @@ struct GemmArgs {
   uint16_t *y;
   int y_cs, y_co;
   int relu;
+  // data gradients: zero where this activation (of the output's grid and channels,
+  // a ReLU's output) is not positive; NULL for none
+  const uint16_t *act;
+  int act_cs, act_co;
 };
 
 // Wave tile TM x TN MFMA tiles (32 x 32 each): per K step a lane loads TM A
@@ -349,6 +353,18 @@ __device__ __forceinline__ uint32_t f2bf_pair(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
+// v, zero where the ReLU output y is not positive.
+__device__ __forceinline__ uint4 relu_masked(const uint4 &v, const uint4 &y) {
+  const uint32_t yy[4] = {y.x, y.y, y.z, y.w};
+  uint32_t gg[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (!(bf2f((uint16_t)(yy[k] & 0xffffu)) > 0.f)) gg[k] &= 0xffff0000u;
+    if (!(bf2f((uint16_t)(yy[k] >> 16)) > 0.f)) gg[k] &= 0x0000ffffu;
+  }
+  return make_uint4(gg[0], gg[1], gg[2], gg[3]);
+}
+
 // Output of a transposed 32 x 32 product tile: this lane holds channels
 // c0 + 8 q + 4 half + 0..3 of pixel o in registers 4 q .. 4 q + 3.  Bias (loaded
 // beforehand: a load between two tiles' stores would wait for the first's), ReLU
@@ -367,8 +383,23 @@ __device__ __forceinline__ BiasRun load_bias(__amdgpu_buffer_rsrc_t buffer, int 
   return r;
 }
 
-__device__ __forceinline__ void store_pixel(const GemmArgs &a, const BiasRun &bias, const floatx16 &acc, bool in,
-                                            int64_t o, int c0, int half) {
+// The activation of the runs store_pixel writes (loaded beforehand, as the bias).
+struct ActRun {
+  uint4 y[2];
+};
+__device__ __forceinline__ ActRun load_act(const GemmArgs &a, bool in, int64_t o, int c0, int half) {
+  ActRun r = {};
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int c = c0 + 16 * q + 8 * half;
+    if (in && c < a.nout) r.y[q] = *reinterpret_cast<const uint4 *>(a.act + o * a.act_cs + a.act_co + c);
+  }
+  return r;
+}
+
+template <bool ACT>
+__device__ __forceinline__ void store_pixel(const GemmArgs &a, const BiasRun &bias, const ActRun &act, const floatx16 &acc,
+                                            bool in, int64_t o, int c0, int half) {
   uint32_t w[8];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -389,7 +420,9 @@ __device__ __forceinline__ void store_pixel(const GemmArgs &a, const BiasRun &bi
     const auto s0 = __builtin_amdgcn_permlane32_swap(w[4 * q], w[4 * q + 2], false, false);
     const auto s1 = __builtin_amdgcn_permlane32_swap(w[4 * q + 1], w[4 * q + 3], false, false);
     const int c = 16 * q + 8 * half;
-    if (in && c0 + c < a.nout) *reinterpret_cast<uint4 *>(y + c) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+    uint4 v = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+    if (ACT && a.act) v = relu_masked(v, act.y[q]);
+    if (in && c0 + c < a.nout) *reinterpret_cast<uint4 *>(y + c) = v;
   }
 }
 
@@ -584,6 +617,16 @@ __global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
       if (s + i < steps) products(i);
   }
   // C[channel 8 (r / 4) + 4 half + r % 4][pixel l31]
+  ActRun act[ORDER == 3 ? 1 : TM][ORDER == 3 ? 1 : TN] = {};
+  if (ORDER != 3 && a.act) {
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int u = 0; u < TN; ++u) {
+        const int64_t p = pix0 + 32 * t + l31;
+        act[ORDER == 3 ? 0 : t][ORDER == 3 ? 0 : u] = load_act(a, p < P, p, col0 + 32 * u, half);
+      }
+  }
 #pragma unroll
   for (int t = 0; t < TM; ++t) {
     const int64_t p = pix0 + 32 * t + l31;
@@ -595,7 +638,7 @@ __global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
         o = (2 * r + (u >> 1)) * W2 + 2 * (p - r * a.w) + (u & 1);
       }
       const int c0 = col0 + (ORDER == 3 ? 0 : 32 * u);
-      store_pixel(a, b[ORDER == 3 ? 0 : u], acc[t][u], p < P, o, c0, half);
+      store_pixel<ORDER != 3>(a, b[ORDER == 3 ? 0 : u], act[ORDER == 3 ? 0 : t][ORDER == 3 ? 0 : u], acc[t][u], p < P, o, c0, half);
     }
   }
 }
@@ -625,7 +668,7 @@ __global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
 constexpr int kConvThreads = 512;
 constexpr int kConvTilePix = 512;
 
-template <int TN>
+template <int TN, bool ACT>
 __global__ __launch_bounds__(kConvThreads, TN == 1 ? 4 : 2) void conv3x3_rows(GemmArgs a, int items) {
   constexpr int TM = 4, BC = 32 * TN;
   constexpr int kPix = (TM + 2) * 130;  // staged pixels, most for 128 columns
@@ -768,14 +811,24 @@ __global__ __launch_bounds__(kConvThreads, TN == 1 ? 4 : 2) void conv3x3_rows(Ge
     BiasRun b[TN];
 #pragma unroll
     for (int u = 0; u < TN; ++u) b[u] = load_bias(bias, q.col0 + 32 * u, half);
+    const int y0 = q.y0 + row0;
+    const int64_t o = ((int64_t)q.img * h + y0) * w + q.x0 + x;
 #pragma unroll
-    for (int t = 0; t < TM; ++t) {
-      const int y = q.y0 + row0 + t;
-      const int64_t o = ((int64_t)q.img * h + y) * w + q.x0 + x;
+    for (int u = 0; u < TN; ++u) {
+      constexpr int TA = TN == 1 ? 2 : TM;  // rows whose activations the registers hold
 #pragma unroll
-      for (int u = 0; u < TN; ++u) {
-        store_pixel(a, b[u], acc[t][u], y < h, o, q.col0 + 32 * u, half);
-        acc[t][u] = floatx16{};
+      for (int t0 = 0; t0 < TM; t0 += TA) {
+        ActRun act[TA] = {};
+        if constexpr (ACT) {
+#pragma unroll
+          for (int t = 0; t < TA; ++t)
+            act[t] = load_act(a, y0 + t0 + t < h, o + (int64_t)(t0 + t) * w, q.col0 + 32 * u, half);
+        }
+#pragma unroll
+        for (int t = t0; t < t0 + TA; ++t) {
+          store_pixel<ACT>(a, b[u], act[t - t0], acc[t][u], y0 + t < h, o + (int64_t)t * w, q.col0 + 32 * u, half);
+          acc[t][u] = floatx16{};
+        }
       }
     }
   }
@@ -827,6 +880,7 @@ static void launch_direct_tiles(const GemmArgs &a, int64_t P, hipStream_t s) {
 // within the buffer window, and its tiles within a grid.
 static bool direct_fits(const GemmArgs &a, int64_t P, int taps) {
   if (reinterpret_cast<uintptr_t>(a.y) % 16 || a.y_cs % 8 || a.y_co % 8 || a.nout % 8) return false;
+  if (a.act && (reinterpret_cast<uintptr_t>(a.act) % 16 || a.act_cs % 8 || a.act_co % 8)) return false;
   const int64_t reach = (taps == 9 ? 64 + 2 * (int64_t)a.w + 2 : 2 * (64 + 2 * (int64_t)a.w) * 2) * a.x_cs * 2;
   const int64_t wbytes = (int64_t)64 * taps * a.kc * 2;
   return reach < kWholeBuffer && wbytes < ((int64_t)1 << 29) && ((P + 31) / 32) * ((a.nout + 31) / 32) < ((int64_t)1 << 31);
@@ -846,9 +900,12 @@ template <int TN>
 static void launch_conv_rows(const GemmArgs &a, hipStream_t s) {
   // one tile of 64 channels, two of 32 per CU at a time
   const int64_t tiles = conv_rows_tiles(a, 32 * TN), most = TN == 1 ? 512 : 256;
-  conv3x3_rows<TN><<<dim3((unsigned)(tiles < most ? (tiles + 7) / 8 * 8 : most)), kConvThreads, 0, s>>>(a, (int)tiles);
+  const dim3 g((unsigned)(tiles < most ? (tiles + 7) / 8 * 8 : most));
+  if (a.act) conv3x3_rows<TN, true><<<g, kConvThreads, 0, s>>>(a, (int)tiles);
+  else conv3x3_rows<TN, false><<<g, kConvThreads, 0, s>>>(a, (int)tiles);
 }
 
+// (Returns whether an activation's mask has been applied.)
 // Group by group where the staged kernels can run (a rule on the shape alone: the
 // order of the sums may not change with the number of images), tap by tap elsewhere.
 // Within the first, by tiles of 512 pixels x 32 channels, us direct / through LDS:
@@ -857,7 +914,7 @@ static void launch_conv_rows(const GemmArgs &a, hipStream_t s) {
 //   32 -> 32 at 1 x 256 x 256 (128) 7.1 / 7.9, at two (256) 11.1 / 9.1.
 // 64-channel tiles once there is one per CU: 64 -> 64 at 4 x 128 x 128 13.9 (13.1
 // with 32), at eight images 18.7 (21.5).
-static void launch_conv3x3(const GemmArgs &a, int64_t P, hipStream_t s) {
+static bool launch_conv3x3(const GemmArgs &a, int64_t P, hipStream_t s) {
   const bool direct = direct_fits(a, P, 9);
   if (direct && a.kc == 8) {
     if (P >= 2 * 32 * 1024) launch_direct<2, 2, 1>(a, P, s);
@@ -870,12 +927,17 @@ static void launch_conv3x3(const GemmArgs &a, int64_t P, hipStream_t s) {
     // vectors: 64 blocks of the staged kernel leave most CUs idle
     const dim3 g((unsigned)(P / kConvBlockPix), (unsigned)((a.nout + 63) / 64));
     if (direct && (a.w >= 32 || (int64_t)g.x * g.y <= 64)) launch_direct_tiles<0>(a, P, s);
-    else conv3x3_lds<<<g, 256, 0, s>>>(a);
+    else {
+      conv3x3_lds<<<g, 256, 0, s>>>(a);
+      return false;
+    }
   } else if (direct && a.kc % 16 == 0) {
     launch_direct_tiles<1>(a, P, s);
   } else {
     launch_gather<0>(a, P, 1, s);
+    return false;
   }
+  return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -1656,7 +1718,7 @@ __global__ __launch_bounds__(256) void maxpool_fwd_vec(const uint16_t *x, unsign
 
 __global__ __launch_bounds__(256) void maxpool_bwd_vec(const uint16_t *x, unsigned total, int w, int c8, int x_cs,
                                                        int x_co, const uint16_t *dy, int dy_cs, int dy_co, uint16_t *dx,
-                                                       int dx_cs, int dx_co, int accumulate) {
+                                                       int dx_cs, int dx_co, int accumulate, int relu) {
   const unsigned e = blockIdx.x * 256u + threadIdx.x;
   if (e >= total) return;
   const Window o = pool_window(e, (unsigned)w / 2, (unsigned)c8, w);
@@ -1693,7 +1755,9 @@ __global__ __launch_bounds__(256) void maxpool_bwd_vec(const uint16_t *x, unsign
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       if (k == arg[j]) t[j] = accumulate ? f2bf(bf2f(t[j]) + bf2f(g[j])) : g[j];
-    *reinterpret_cast<bf16x8 *>(pd + (int64_t)((k >> 1) * w + (k & 1)) * dx_cs) = pack8(t);
+    uint4 r = __builtin_bit_cast(uint4, pack8(t));
+    if (relu) r = relu_masked(r, v[k]);
+    *reinterpret_cast<uint4 *>(pd + (int64_t)((k >> 1) * w + (k & 1)) * dx_cs) = r;
   }
 }
 
@@ -1707,15 +1771,8 @@ __global__ void relu_bwd_vec(const uint16_t *y, int64_t n_pix, int c8, int y_cs,
     const int ch = (int)(e - p * c8) * 8;
     const uint4 yv = *reinterpret_cast<const uint4 *>(y + p * y_cs + y_co + ch);
     uint4 *dp = reinterpret_cast<uint4 *>(dy + p * dy_cs + dy_co + ch);
-    uint4 g = *dp;
-    const uint32_t yy[4] = {yv.x, yv.y, yv.z, yv.w};
-    uint32_t gg[4] = {g.x, g.y, g.z, g.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (!(bf2f((uint16_t)(yy[k] & 0xffffu)) > 0.f)) gg[k] &= 0xffff0000u;
-      if (!(bf2f((uint16_t)(yy[k] >> 16)) > 0.f)) gg[k] &= 0x0000ffffu;
-    }
-    *dp = make_uint4(gg[0], gg[1], gg[2], gg[3]);
+    const uint4 g = *dp;
+    *dp = relu_masked(g, yv);
   }
 }
 
@@ -1807,7 +1864,7 @@ __global__ void head_loss_pix(const uint16_t *x, int64_t n_pix, int c, int x_cs,
 __global__ __launch_bounds__(256) void head_loss_pix_v(const uint16_t *x, int64_t n_pix, int c, int x_cs,
                                                        const float *w, const float *b, const float *t,
                                                        const uint8_t *mask, float scale, uint16_t *dx, float *g_out,
-                                                       float *l_out) {
+                                                       float *l_out, int relu) {
   __shared__ __attribute__((aligned(16))) char sx[256 * (64 * 2 + 16)];
   __shared__ float sw[64], sg[256];
   const int tid = threadIdx.x, c8 = c / 8, pitch = 2 * c + 16;  // (the odd 16 bytes spread pixels over the banks)
@@ -1850,7 +1907,9 @@ __global__ __launch_bounds__(256) void head_loss_pix_v(const uint16_t *x, int64_
     uint32_t u[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) u[j] = f2bf_pair(sg[q] * sw[8 * k + 2 * j], sg[q] * sw[8 * k + 2 * j + 1]);
-    *reinterpret_cast<uint4 *>(dx + (p0 + q) * c + 8 * k) = make_uint4(u[0], u[1], u[2], u[3]);
+    uint4 r = make_uint4(u[0], u[1], u[2], u[3]);
+    if (relu) r = relu_masked(r, *reinterpret_cast<const uint4 *>(sx + q * pitch + 16 * k));
+    *reinterpret_cast<uint4 *>(dx + (p0 + q) * c + 8 * k) = r;
   }
 }
 
@@ -2043,6 +2102,27 @@ int unet_conv3x3_fwd(const uint16_t *x, int n, int h, int w, int cin, int x_cs, 
   return launched();
 }
 
+static void launch_relu_bwd(const uint16_t *y, int64_t n_pix, int c, int y_cs, int y_co, uint16_t *dy, int dy_cs,
+                            int dy_co, hipStream_t s) {
+  if (c % 8 == 0 && y_cs % 8 == 0 && y_co % 8 == 0 && dy_cs % 8 == 0 && dy_co % 8 == 0)
+    relu_bwd_vec<<<grid1d(n_pix * (c / 8)), 256, 0, s>>>(y, n_pix, c / 8, y_cs, y_co, dy, dy_cs, dy_co);
+  else
+    relu_bwd_kernel<<<grid1d(n_pix * c), 256, 0, s>>>(y, n_pix, c, y_cs, y_co, dy, dy_cs, dy_co);
+}
+
+int unet_conv3x3_relu_bwd_data(const uint16_t *dy, int n, int h, int w, int cout, int dy_cs, int dy_co,
+                               const uint16_t *wt, int cin, uint16_t *dx, int dx_cs, int dx_co, const uint16_t *act,
+                               int act_cs, int act_co, void *s) {
+  if (!dy || !wt || !dx || !act || n < 1 || h < 1 || w < 1 || !ok8(cout) || dy_cs % 8 || dy_co % 8 ||
+      !slice_ok(dy_co, cout, dy_cs) || !slice_ok(dx_co, cin, dx_cs) || !slice_ok(act_co, cin, act_cs))
+    return -1;
+  GemmArgs a{dy, n, h, w, cout, dy_cs, dy_co, wt, nullptr, cin, dx, dx_cs, dx_co, 0, act, act_cs, act_co};
+  const int64_t P = (int64_t)n * h * w;
+  if (!launch_conv3x3(a, P, (hipStream_t)s))
+    launch_relu_bwd(act, P, cin, act_cs, act_co, dx, dx_cs, dx_co, (hipStream_t)s);
+  return launched();
+}
+
 int unet_conv3x3_flip(const uint16_t *wgt, int cout, int cin, uint16_t *wt, void *s) {
   if (!wgt || !wt || cout < 1 || cin < 1) return -1;
   conv_flip<<<grid1d((int64_t)cout * 9 * cin), 256, 0, (hipStream_t)s>>>(wgt, cout, cin, wt);
@@ -2088,12 +2168,7 @@ int unet_conv3x3_wgrad_noalloc(const uint16_t *x, int n, int h, int w, int cin, 
 int unet_relu_bwd(const uint16_t *y, int n_pix, int c, int y_cs, int y_co, uint16_t *dy, int dy_cs, int dy_co,
                   void *s) {
   if (!y || !dy || n_pix < 1 || !slice_ok(y_co, c, y_cs) || !slice_ok(dy_co, c, dy_cs)) return -1;
-  if (c % 8 == 0 && y_cs % 8 == 0 && y_co % 8 == 0 && dy_cs % 8 == 0 && dy_co % 8 == 0)
-    relu_bwd_vec<<<grid1d((int64_t)n_pix * (c / 8)), 256, 0, (hipStream_t)s>>>(y, n_pix, c / 8, y_cs, y_co, dy,
-                                                                                dy_cs, dy_co);
-  else
-    relu_bwd_kernel<<<grid1d((int64_t)n_pix * c), 256, 0, (hipStream_t)s>>>(y, n_pix, c, y_cs, y_co, dy, dy_cs,
-                                                                            dy_co);
+  launch_relu_bwd(y, n_pix, c, y_cs, y_co, dy, dy_cs, dy_co, (hipStream_t)s);
   return launched();
 }
 
@@ -2112,19 +2187,31 @@ int unet_maxpool_fwd(const uint16_t *x, int n, int h, int w, int c, int x_cs, in
   return launched();
 }
 
-int unet_maxpool_bwd(const uint16_t *x, int n, int h, int w, int c, int x_cs, int x_co, const uint16_t *dy,
-                     int dy_cs, int dy_co, uint16_t *dx, int dx_cs, int dx_co, int accumulate, void *s) {
+static int maxpool_bwd(const uint16_t *x, int n, int h, int w, int c, int x_cs, int x_co, const uint16_t *dy, int dy_cs,
+                       int dy_co, uint16_t *dx, int dx_cs, int dx_co, int accumulate, int relu, void *s) {
   if (!x || !dy || !dx || n < 1 || h < 2 || w < 2 || (h & 1) || (w & 1) || !slice_ok(x_co, c, x_cs) ||
       !slice_ok(dy_co, c, dy_cs) || !slice_ok(dx_co, c, dx_cs))
     return -1;
   const int64_t vectors = (int64_t)n * h * w * c / 32;
-  if (vec8(x, c, x_cs, x_co) && vec8(dy, c, dy_cs, dy_co) && vec8(dx, c, dx_cs, dx_co) && vectors < ((int64_t)1 << 31))
+  if (vec8(x, c, x_cs, x_co) && vec8(dy, c, dy_cs, dy_co) && vec8(dx, c, dx_cs, dx_co) && vectors < ((int64_t)1 << 31)) {
     maxpool_bwd_vec<<<(unsigned)((vectors + 255) / 256), 256, 0, (hipStream_t)s>>>(
-        x, (unsigned)vectors, w, c / 8, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate);
-  else
-    maxpool_bwd_kernel<<<grid1d((int64_t)n * h * w * c / 4), 256, 0, (hipStream_t)s>>>(
-        x, n, h, w, c, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate);
+        x, (unsigned)vectors, w, c / 8, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate, relu);
+    return launched();
+  }
+  maxpool_bwd_kernel<<<grid1d((int64_t)n * h * w * c / 4), 256, 0, (hipStream_t)s>>>(
+      x, n, h, w, c, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate);
+  if (relu) launch_relu_bwd(x, (int64_t)n * h * w, c, x_cs, x_co, dx, dx_cs, dx_co, (hipStream_t)s);
   return launched();
+}
+
+int unet_maxpool_bwd(const uint16_t *x, int n, int h, int w, int c, int x_cs, int x_co, const uint16_t *dy,
+                     int dy_cs, int dy_co, uint16_t *dx, int dx_cs, int dx_co, int accumulate, void *s) {
+  return maxpool_bwd(x, n, h, w, c, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate, 0, s);
+}
+
+int unet_maxpool_relu_bwd(const uint16_t *x, int n, int h, int w, int c, int x_cs, int x_co, const uint16_t *dy,
+                          int dy_cs, int dy_co, uint16_t *dx, int dx_cs, int dx_co, int accumulate, void *s) {
+  return maxpool_bwd(x, n, h, w, c, x_cs, x_co, dy, dy_cs, dy_co, dx, dx_cs, dx_co, accumulate, 1, s);
 }
 
 int unet_upconv_fwd(const uint16_t *x, int n, int h, int w, int cin, int x_cs, int x_co, const uint16_t *wgt,
@@ -2142,18 +2229,35 @@ int unet_upconv_fwd(const uint16_t *x, int n, int h, int w, int cin, int x_cs, i
   return launched();
 }
 
-int unet_upconv_bwd_data(const uint16_t *dy, int n, int h, int w, int cout, int dy_cs, int dy_co,
-                         const uint16_t *wgt, int cin, uint16_t *wt, uint16_t *dx, int dx_cs, int dx_co, void *s) {
+static int upconv_bwd_data(const uint16_t *dy, int n, int h, int w, int cout, int dy_cs, int dy_co,
+                           const uint16_t *wgt, int cin, uint16_t *wt, uint16_t *dx, int dx_cs, int dx_co,
+                           const uint16_t *act, int act_cs, int act_co, void *s) {
   if (!dy || !wgt || !wt || !dx || n < 1 || h < 1 || w < 1 || !ok8(cout) || dy_cs % 8 || dy_co % 8 ||
       !slice_ok(dy_co, cout, dy_cs) || !slice_ok(dx_co, cin, dx_cs))
     return -1;
   up_rearrange<<<grid1d((int64_t)cout * 4 * cin), 256, 0, (hipStream_t)s>>>(wgt, cout, cin, wt);
   // A = dy over the 2h x 2w grid gathered at 2p + tap, output grid h x w
-  GemmArgs a{dy, n, h, w, cout, dy_cs, dy_co, wt, nullptr, cin, dx, dx_cs, dx_co, 0};
+  GemmArgs a{dy, n, h, w, cout, dy_cs, dy_co, wt, nullptr, cin, dx, dx_cs, dx_co, 0, act, act_cs, act_co};
   const int64_t P = (int64_t)n * h * w;
-  if (cout % 16 == 0 && direct_fits(a, P, 4)) launch_direct_tiles<4>(a, P, (hipStream_t)s);
-  else launch_gather<2>(a, P, 1, (hipStream_t)s);
+  if (cout % 16 == 0 && direct_fits(a, P, 4)) {
+    launch_direct_tiles<4>(a, P, (hipStream_t)s);
+  } else {
+    launch_gather<2>(a, P, 1, (hipStream_t)s);
+    if (act) launch_relu_bwd(act, P, cin, act_cs, act_co, dx, dx_cs, dx_co, (hipStream_t)s);
+  }
   return launched();
+}
+
+int unet_upconv_bwd_data(const uint16_t *dy, int n, int h, int w, int cout, int dy_cs, int dy_co,
+                         const uint16_t *wgt, int cin, uint16_t *wt, uint16_t *dx, int dx_cs, int dx_co, void *s) {
+  return upconv_bwd_data(dy, n, h, w, cout, dy_cs, dy_co, wgt, cin, wt, dx, dx_cs, dx_co, nullptr, 0, 0, s);
+}
+
+int unet_upconv_relu_bwd_data(const uint16_t *dy, int n, int h, int w, int cout, int dy_cs, int dy_co,
+                              const uint16_t *wgt, int cin, uint16_t *wt, uint16_t *dx, int dx_cs, int dx_co,
+                              const uint16_t *act, int act_cs, int act_co, void *s) {
+  if (!act || !slice_ok(act_co, cin, act_cs)) return -1;
+  return upconv_bwd_data(dy, n, h, w, cout, dy_cs, dy_co, wgt, cin, wt, dx, dx_cs, dx_co, act, act_cs, act_co, s);
 }
 
 int unet_upconv_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs, int x_co, const uint16_t *dy,
@@ -2183,9 +2287,9 @@ int64_t unet_head_scratch_floats(int n_pix, int c) {
   return 2 * (int64_t)n_pix + blocks * (2 + c);
 }
 
-int unet_head_loss_bwd(const uint16_t *x, int n_pix, int c, int x_cs, const float *w, const float *b,
+static int head_loss_bwd(const uint16_t *x, int n_pix, int c, int x_cs, const float *w, const float *b,
                        const float *target, const uint8_t *mask, float scale, float *loss, uint16_t *dx,
-                       float *dw, float *db, float *partial, void *s) {
+                       float *dw, float *db, float *partial, int relu, void *s) {
   if (!x || !w || !b || !target || !mask || !loss || !partial || n_pix < 1 || c < 1 || c > 256 || 256 % c ||
       c > x_cs)
     return -1;
@@ -2193,15 +2297,29 @@ int unet_head_loss_bwd(const uint16_t *x, int n_pix, int c, int x_cs, const floa
   const int blocks = (int)(((int64_t)n_pix + kHeadPix - 1) / kHeadPix);
   if (c <= 64 && vec8(x, c, x_cs, 0) && (!dx || vec8(dx, c, c, 0)))
     head_loss_pix_v<<<(n_pix + 255) / 256, 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, w, b, target, mask, scale, dx, g,
-                                                                     l);
-  else
+                                                                     l, relu);
+  else {
     head_loss_pix<<<grid1d(n_pix), 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, w, b, target, mask, scale, dx, g, l);
+    if (relu && dx) launch_relu_bwd(x, n_pix, c, x_cs, 0, dx, c, 0, (hipStream_t)s);
+  }
   if ((c & 7) == 0 && (x_cs & 7) == 0)
     head_loss_sums_v<<<blocks, 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, g, l, sums);
   else
     head_loss_sums<<<blocks, 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, g, l, sums);
   head_loss_final<<<(2 + c + 31) / 32, 256, 0, (hipStream_t)s>>>(sums, blocks, c, loss, dw, db);
   return launched();
+}
+
+int unet_head_loss_bwd(const uint16_t *x, int n_pix, int c, int x_cs, const float *w, const float *b,
+                       const float *target, const uint8_t *mask, float scale, float *loss, uint16_t *dx,
+                       float *dw, float *db, float *partial, void *s) {
+  return head_loss_bwd(x, n_pix, c, x_cs, w, b, target, mask, scale, loss, dx, dw, db, partial, 0, s);
+}
+
+int unet_head_loss_relu_bwd(const uint16_t *x, int n_pix, int c, int x_cs, const float *w, const float *b,
+                       const float *target, const uint8_t *mask, float scale, float *loss, uint16_t *dx,
+                       float *dw, float *db, float *partial, void *s) {
+  return head_loss_bwd(x, n_pix, c, x_cs, w, b, target, mask, scale, loss, dx, dw, db, partial, 1, s);
 }
 
 int unet_adam(float *p, const float *g, float *m, float *v, uint16_t *p_bf16, int64_t count, float lr, float beta1,

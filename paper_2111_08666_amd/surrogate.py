@@ -42,6 +42,11 @@ def lib():
             "unet_relu_bwd": [vp, i32, i32, i32, i32, vp, i32, i32, vp],
             "unet_maxpool_fwd": [vp, i32, i32, i32, i32, i32, i32, vp, i32, i32, vp],
             "unet_maxpool_bwd": [vp, i32, i32, i32, i32, i32, i32, vp, i32, i32, vp, i32, i32, i32, vp],
+            "unet_maxpool_relu_bwd": [vp, i32, i32, i32, i32, i32, i32, vp, i32, i32, vp, i32, i32, i32, vp],
+            "unet_conv3x3_relu_bwd_data": [vp, i32, i32, i32, i32, i32, i32, vp, i32, vp, i32, i32, vp, i32, i32, vp],
+            "unet_upconv_relu_bwd_data": [vp, i32, i32, i32, i32, i32, i32, vp, i32, vp, vp, i32, i32, vp, i32, i32,
+                                          vp],
+            "unet_head_loss_relu_bwd": [vp, i32, i32, i32, vp, vp, vp, vp, f32, vp, vp, vp, vp, vp, vp],
             "unet_upconv_fwd": [vp, i32, i32, i32, i32, i32, i32, vp, vp, i32, vp, i32, i32, vp],
             "unet_upconv_bwd_data": [vp, i32, i32, i32, i32, i32, i32, vp, i32, vp, vp, i32, i32, vp],
             "unet_upconv_wgrad": [vp, i32, i32, i32, i32, i32, i32, vp, i32, i32, i32, vp, vp, vp, vp],
@@ -66,6 +71,7 @@ def lib():
 EXPORTS = [
     "unet_mfma_probe", "unet_conv3x3_fwd", "unet_conv3x3_flip", "unet_wgrad_scratch_floats",
     "unet_conv3x3_wgrad", "unet_conv3x3_wgrad_noalloc", "unet_relu_bwd", "unet_maxpool_fwd", "unet_maxpool_bwd", "unet_upconv_fwd",
+    "unet_conv3x3_relu_bwd_data", "unet_upconv_relu_bwd_data", "unet_maxpool_relu_bwd", "unet_head_loss_relu_bwd",
     "unet_upconv_bwd_data", "unet_upconv_wgrad", "unet_head_fwd", "unet_head_scratch_floats",
     "unet_head_loss_bwd", "unet_adam", "unet_to_bf16", "unet_to_f32",
 ]
@@ -310,52 +316,56 @@ class UNet:
         if count is None:
             count = int(mask.sum().item())
         scale = 1.0 / max(count, 1)
-        call("unet_head_loss_bwd", ptr(A["dec0b"]), n * h * w, c[0], c[0], self._p32("head.w"),
+        call("unet_head_loss_relu_bwd", ptr(A["dec0b"]), n * h * w, c[0], c[0], self._p32("head.w"),
              self._p32("head.b"), ptr(target), ptr(mask), scale, ptr(self.loss), ptr(G["dec0b"]),
              self._g("head.w"), self._g("head.b"), ptr(self.head_scratch), s)
         wt, part = self.wt, self.partial
 
-        def conv_back(x, x_cs, x_co, y, y_cs, y_co, gy, gy_cs, gy_co, hh, ww, cin, cout, name, gx, gx_cs, gx_co):
-            """Through act(conv(x)) = y: mask gy by ReLU, weight/bias grads,
-            and (if gx is given) the data gradient into gx."""
-            call("unet_relu_bwd", ptr(y), n * hh * ww, cout, y_cs, y_co, ptr(gy), gy_cs, gy_co, s)
+        def conv_back(x, x_cs, x_co, gy, gy_cs, gy_co, hh, ww, cin, cout, name, gx, gx_cs, gx_co, act=None):
+            """Through the 3x3 convolution `name` of x, given its output's
+            gradient gy (already through the ReLU): weight/bias grads, and (if
+            gx is given) the data gradient into gx, through the ReLU whose
+            output act is (act = x, or None for none)."""
             call("unet_conv3x3_wgrad", ptr(x), n, hh, ww, cin, x_cs, x_co, ptr(gy), cout, gy_cs, gy_co,
                  self._g(name + ".w"), self._g(name + ".b"), ptr(part), 0, s)
-            if gx is not None:
-                call("unet_conv3x3_flip", self._w(name), cout, cin, ptr(wt), s)
+            if gx is None:
+                return
+            call("unet_conv3x3_flip", self._w(name), cout, cin, ptr(wt), s)
+            if act is None:
                 call("unet_conv3x3_fwd", ptr(gy), n, hh, ww, cout, gy_cs, gy_co, ptr(wt), None, cin, ptr(gx),
                      gx_cs, gx_co, 0, s)
+            else:
+                call("unet_conv3x3_relu_bwd_data", ptr(gy), n, hh, ww, cout, gy_cs, gy_co, ptr(wt), cin, ptr(gx),
+                     gx_cs, gx_co, ptr(act), x_cs, x_co, s)
 
         for k in range(self.L - 1):
             hk, wk = self.hs[k]
             h1, w1 = self.hs[k + 1]
-            conv_back(A[f"dec{k}a"], c[k], 0, A[f"dec{k}b"], c[k], 0, G[f"dec{k}b"], c[k], 0, hk, wk, c[k], c[k],
-                      f"dec{k}b", G[f"dec{k}a"], c[k], 0)
-            conv_back(A[f"cat{k}"], 2 * c[k], 0, A[f"dec{k}a"], c[k], 0, G[f"dec{k}a"], c[k], 0, hk, wk, 2 * c[k],
-                      c[k], f"dec{k}a", G[f"cat{k}"], 2 * c[k], 0)
+            conv_back(A[f"dec{k}a"], c[k], 0, G[f"dec{k}b"], c[k], 0, hk, wk, c[k], c[k], f"dec{k}b", G[f"dec{k}a"],
+                      c[k], 0, act=A[f"dec{k}a"])
+            conv_back(A[f"cat{k}"], 2 * c[k], 0, G[f"dec{k}a"], c[k], 0, hk, wk, 2 * c[k], c[k], f"dec{k}a",
+                      G[f"cat{k}"], 2 * c[k], 0)
             below = A[f"dec{k + 1}b"] if k + 1 < self.L - 1 else A[f"enc{self.L - 1}b"]
             gbelow = G[f"dec{k + 1}b"] if k + 1 < self.L - 1 else G[f"enc{self.L - 1}b"]
             call("unet_upconv_wgrad", ptr(below), n, h1, w1, c[k + 1], c[k + 1], 0, ptr(G[f"cat{k}"]), c[k],
                  2 * c[k], c[k], self._g(f"up{k}.w"), self._g(f"up{k}.b"), ptr(part), s)
-            call("unet_upconv_bwd_data", ptr(G[f"cat{k}"]), n, h1, w1, c[k], 2 * c[k], c[k], self._w(f"up{k}"),
-                 c[k + 1], ptr(wt), ptr(gbelow), c[k + 1], 0, s)
+            call("unet_upconv_relu_bwd_data", ptr(G[f"cat{k}"]), n, h1, w1, c[k], 2 * c[k], c[k], self._w(f"up{k}"),
+                 c[k + 1], ptr(wt), ptr(gbelow), c[k + 1], 0, ptr(below), c[k + 1], 0, s)
         for k in range(self.L - 1, -1, -1):
             hk, wk = self.hs[k]
             if k < self.L - 1:
-                yb, yb_cs, gyb, gyb_cs = A[f"cat{k}"], 2 * c[k], G[f"cat{k}"], 2 * c[k]
-                call("unet_maxpool_bwd", ptr(A[f"cat{k}"]), n, hk, wk, c[k], 2 * c[k], 0, ptr(G[f"pool{k}"]),
-                     c[k], 0, ptr(G[f"cat{k}"]), 2 * c[k], 0, 1, s)
+                gyb, gyb_cs = G[f"cat{k}"], 2 * c[k]
+                call("unet_maxpool_relu_bwd", ptr(A[f"cat{k}"]), n, hk, wk, c[k], 2 * c[k], 0, ptr(G[f"pool{k}"]),
+                     c[k], 0, ptr(gyb), gyb_cs, 0, 1, s)
             else:
-                yb, yb_cs, gyb, gyb_cs = A[f"enc{k}b"], c[k], G[f"enc{k}b"], c[k]
-            conv_back(A[f"enc{k}a"], c[k], 0, yb, yb_cs, 0, gyb, gyb_cs, 0, hk, wk, c[k], c[k], f"enc{k}b",
-                      G[f"enc{k}a"], c[k], 0)
+                gyb, gyb_cs = G[f"enc{k}b"], c[k]
+            conv_back(A[f"enc{k}a"], c[k], 0, gyb, gyb_cs, 0, hk, wk, c[k], c[k], f"enc{k}b", G[f"enc{k}a"], c[k], 0,
+                      act=A[f"enc{k}a"])
             if k > 0:
                 x, x_c = A[f"pool{k - 1}"], c[k - 1]
-                conv_back(x, x_c, 0, A[f"enc{k}a"], c[k], 0, G[f"enc{k}a"], c[k], 0, hk, wk, x_c, c[k],
-                          f"enc{k}a", G[f"pool{k - 1}"], x_c, 0)
+                conv_back(x, x_c, 0, G[f"enc{k}a"], c[k], 0, hk, wk, x_c, c[k], f"enc{k}a", G[f"pool{k - 1}"], x_c, 0)
             else:
-                conv_back(A["x"], IN_CH, 0, A["enc0a"], c[0], 0, G["enc0a"], c[0], 0, hk, wk, IN_CH, c[0],
-                          "enc0a", None, 0, 0)
+                conv_back(A["x"], IN_CH, 0, G["enc0a"], c[0], 0, hk, wk, IN_CH, c[0], "enc0a", None, 0, 0)
         return self.loss
 
     def adam(self, lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8):
