@@ -456,6 +456,8 @@ __device__ __forceinline__ void ccomplete9(const InstDev &d, gcf *__restrict__ f
 // waves (24 uneven instances: 104.9 against 115.1 us): its rank lookups cost
 // more per row than the registers of a second row; in FP64 eight win there
 // too (165 against 188-196).
+// (With the collision's algebra per opposite pair, since then: 1024 x 512 17.0,
+// 24 uneven instances 101.5.)
 // Four waves with TY = 12, and with TY = 8 in FP32, park the last interior row of
 // each wave in LDS between the phases, to fit four and six waves per SIMD.
 template <int TY, typename R, int ST, int CL> struct FusedShape {
@@ -1389,10 +1391,22 @@ __global__ __launch_bounds__(256) void cpsi_kernel(const InstDev *__restrict__ i
   });
 }
 
+// The compacted D3Q19 collision walks backwards, from the populations that the
+// density pass has read last, where little of a state fits the Infinity Cache
+// (256 MiB); us per step by the size of the two population buffers (FP32 storage),
+// forwards / backwards: 269 MB (96^3 open box) 93.0 / 91.2, 405 MB (110^3) 130 / 133,
+// sphere packings of 128^3 (383 MB) 141 / 145, 160^3 (747 MB) 272 / 259 and 192^3
+// (1.3 GB) 445 / 433.  (Plain instead of streaming stores: 87 us for the 96^3 box
+// alone, but 3 % slower with three such states in flight.)
+static bool collide_backwards(const InstDev &h, int q, int storage) {
+  return q == 19 && storage == 0 && ((2 * 2 * 19 * 4 * (int64_t)h.cpitch) >> 20) >= 560;
+}
+
 template <int Q, int COLL, int ST, typename R>
-__global__ __launch_bounds__(256) void ccollide_kernel(const InstDev *__restrict__ insts, int parity) {
+__global__ __launch_bounds__(256) void ccollide_kernel(const InstDev *__restrict__ insts, int parity, int backwards) {
   const InstDev &d = insts[0];
-  const int64_t c = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
+  const int block = backwards ? (int)gridDim.x - 1 - xcd_block() : xcd_block();
+  const int64_t c = (int64_t)block * blockDim.x + threadIdx.x;
   if (c >= d.nf) return;
   const uint32_t key = gld32(d.ckey, c);
   int x, y, z;
@@ -1845,11 +1859,11 @@ static void launch_compact_q(int q, const InstDev *d, const InstDev &h, int pari
   if (q == 9) {
     crho_kernel<9, ST><<<g, b, 0, s>>>(d, parity);
     if (h.nbnd) cpsi_kernel<9><<<gb, bb, 0, s>>>(d);
-    ccollide_kernel<9, COLL, ST, R><<<g, b, 0, s>>>(d, parity);
+    ccollide_kernel<9, COLL, ST, R><<<g, b, 0, s>>>(d, parity, 0);
   } else {
     crho_kernel<19, ST><<<g, b, 0, s>>>(d, parity);
     if (h.nbnd) cpsi_kernel<19><<<gb, bb, 0, s>>>(d);
-    ccollide_kernel<19, COLL, ST, R><<<g, b, 0, s>>>(d, parity);
+    ccollide_kernel<19, COLL, ST, R><<<g, b, 0, s>>>(d, parity, collide_backwards(h, q, ST));
   }
 }
 
