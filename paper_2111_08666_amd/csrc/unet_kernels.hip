@@ -450,7 +450,7 @@ __device__ __forceinline__ void store_pixel(const GemmArgs &a, const BiasRun &bi
 template <int ORDER, int TM, int TN, int GP = 1>
 __global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
   constexpr bool kConv = ORDER <= 2;
-  constexpr int kRing = ORDER == 0 ? 9 * GP : (ORDER == 2 ? 5 : (ORDER == 3 || (ORDER == 4 && TM * TN == 4) ? 4 : 8));
+  constexpr int kRing = ORDER == 0 ? 9 * GP : (ORDER == 2 ? 5 : (ORDER == 3 || (ORDER == 4 && TM * TN >= 4) ? 4 : 8));
   const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int64_t wid = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t P = (int64_t)a.n * a.h * a.w;
@@ -859,19 +859,33 @@ static void launch_direct(const GemmArgs &a, int64_t P, hipStream_t s) {
   igemm_direct<ORDER, TM, TN, GP><<<dim3((unsigned)((pt * ct + wpb - 1) / wpb)), 64 * wpb, 0, s>>>(a, (int)pt);
 }
 
-// Tile by the number of waves: the largest that still gives the chip's 1024
-// SIMDs a wave each (a small one has the shorter chain and the more waves).
+// Tile by the number of 32 x 32 tiles: a larger one reads its operands less often, in
+// 32-byte pieces that are what these kernels are bound by; a small one has the shorter
+// chain and the more waves.  us with the smaller / the larger:
+//   order 0, 256 -> 256: two 32 x 32 images (512 tiles) 18.2 / 15.1 (64 x 32; 20.3 with
+//     64 x 64), three (768) 26.6 / 20.9 (64 x 64); 32 -> 64, 128 x 128 (1024) 4.9 / 5.2;
+//   order 1, 64 -> 64: 92 x 100 (576) 8.6 / 8.0; 256 -> 256: 40 x 60 (600) 26.1 / 19.0,
+//     two of 60 x 90 (2704) 81.5 / 54.6; 64 -> 32: two of 100 x 180 (1125) 13.0 / 12.2;
+//   order 4, 64 channels, 1 x 128 x 128 (1024) 8.1 / 7.0; 256, 8 x 32 x 32 (2048)
+//     22.6 / 14.9; 64 x 128 tiles for 256, 16 x 32 x 32 (4096) 25.7 / 21.2 and for 128,
+//     16 x 64 x 64 (8192) 28.8 / 23.5.
 template <int ORDER>
 static void launch_direct_tiles(const GemmArgs &a, int64_t P, hipStream_t s) {
-  const int64_t t = ((P + 31) / 32) * ((a.nout + 31) / 32);  // 32 x 32 tiles
-  if constexpr (ORDER == 0) {  // (fewer tiles than 4096 come here)
-    if (t >= 2 * 1024) launch_direct<0, 2, 1>(a, P, s);
+  const int64_t t = ((P + 31) / 32) * ((a.nout + 31) / 32);
+  if constexpr (ORDER == 0) {
+    if (a.kc > 32 && a.nout > 32 && t >= 768) launch_direct<0, 2, 2>(a, P, s);
+    else if (t >= (a.kc > 32 ? 512 : 2048)) launch_direct<0, 2, 1>(a, P, s);
     else if (a.kc % 32 == 0) launch_direct<0, 1, 1, 2>(a, P, s);
     else launch_direct<0, 1, 1>(a, P, s);
+  } else if constexpr (ORDER == 1) {
+    if (a.nout > 32 && t >= 512) launch_direct<1, 2, 2>(a, P, s);
+    else if (t >= 1024) launch_direct<1, 2, 1>(a, P, s);
+    else launch_direct<1, 1, 1>(a, P, s);
   } else {
-    if (a.nout > 32 && t >= 4 * 1024) launch_direct<ORDER, 2, 2>(a, P, s);
-    else if (t >= 2 * 1024) launch_direct<ORDER, 2, 1>(a, P, s);
-    else launch_direct<ORDER, 1, 1>(a, P, s);
+    if (a.nout > 64 && t >= 4096) launch_direct<4, 2, 4>(a, P, s);
+    else if (a.nout > 32 && t >= 1024) launch_direct<4, 2, 2>(a, P, s);
+    else if (t >= 2048) launch_direct<4, 2, 1>(a, P, s);
+    else launch_direct<4, 1, 1>(a, P, s);
   }
 }
 
@@ -2222,7 +2236,11 @@ int unet_upconv_fwd(const uint16_t *x, int n, int h, int w, int cin, int x_cs, i
   GemmArgs a{x, n, h, w, cin, x_cs, x_co, wgt, bias, cout, y, y_cs, y_co, 0};
   const int64_t P = (int64_t)n * h * w;
   if (cin % 16 == 0 && direct_fits(a, P, 4)) {
-    launch_direct<3, 1, 4>(a, P, (hipStream_t)s);
+    // 64 pixels a wave once that leaves 512 waves: weights read half as often.  64 -> 32
+    // channels on 16 x 128 x 128 47 us with 32 pixels, 35 us with 64 (22 us for its
+    // bytes); 256 -> 128 on 8 x 32 x 32 (1024 tiles of 32 x 32) 15 and 12 us.
+    if ((P + 31) / 32 * ((cout + 31) / 32) >= 1024) launch_direct<3, 2, 4>(a, P, (hipStream_t)s);
+    else launch_direct<3, 1, 4>(a, P, (hipStream_t)s);
   } else {
     launch_gather<1>(a, P, 4, (hipStream_t)s);
   }

@@ -54,9 +54,11 @@ def _check(S, y, co, cout, ref, terms):
     (3, 7, 11, 48, 64, 48, 0, 64, 0), (2, 3, 300, 16, 24, 24, 8, 24, 0),
     (1, 257, 259, 16, 40, 16, 0, 40, 0),   # 64 x 32 tiles, four waves a block
     (1, 257, 259, 16, 72, 16, 0, 72, 0),   # 64 x 64 tiles
+    (1, 181, 183, 16, 24, 16, 0, 24, 0), (1, 61, 67, 32, 104, 32, 0, 104, 0),
     # 16-channel groups outermost (whole rows per 256 or 512 pixels)
     (1, 16, 16, 16, 8, 16, 0, 8, 0), (1, 16, 16, 48, 96, 56, 8, 104, 8), (1, 8, 32, 64, 40, 64, 0, 40, 0),
     (3, 4, 128, 32, 24, 32, 0, 32, 8), (2, 256, 128, 16, 24, 16, 0, 24, 0),
+    (2, 32, 32, 48, 256, 48, 0, 256, 0), (3, 32, 32, 64, 248, 64, 0, 248, 0),
     # the same through LDS, in tiles of 512 pixels: last tiles that are not whole, one and an odd
     # number of groups, more tiles than blocks, 64-channel tiles with 32 or fewer in the last
     (33, 24, 32, 48, 8, 48, 0, 8, 0), (8, 12, 64, 64, 104, 72, 8, 120, 8), (33, 2, 128, 48, 40, 48, 0, 40, 0),
@@ -88,6 +90,7 @@ def test_conv3x3(S, n, h, w, cin, cout, xc, xo, yc, yo):
 
 @pytest.mark.parametrize("n,h,w,cin,cout,yc,yo", [
     (1, 1, 1, 16, 16, 16, 0), (1, 1, 35, 32, 48, 64, 16), (3, 7, 5, 64, 32, 64, 32), (1, 129, 257, 16, 32, 32, 0),
+    (1, 129, 257, 80, 16, 16, 0), (1, 129, 257, 144, 32, 40, 8),
     (2, 5, 7, 24, 24, 24, 0),  # general kernel, both ways
     (2, 5, 7, 16, 16, 20, 4),  # general kernel forward
 ])
