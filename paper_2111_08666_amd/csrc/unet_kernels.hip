@@ -445,7 +445,8 @@ __device__ __forceinline__ void store_pixel(const GemmArgs &a, const BiasRun &bi
 // Both orders of the 3x3 reduction stay because a change of order changes
 // results in the last place, which a whole network carries on.
 // One 256 x 256 image through the network: 341 us with the staged and gathering
-// kernels alone, 207 us with this one where it is chosen, the same bits.
+// kernels alone, 207 us with this one for all that they left idle, 161 us with
+// conv3x3_rows from 64 tiles on; the same bits.
 // ---------------------------------------------------------------------------
 template <int ORDER, int TM, int TN, int GP = 1>
 __global__ __launch_bounds__(256) void igemm_direct(GemmArgs a, int pix_tiles) {
