@@ -222,152 +222,19 @@ __device__ __forceinline__ void departure(int i, float f, R rho, R ux, R uy, R u
 // u: common velocity (with the half-force shift), F: this component's force.
 // COLL: 0 SRT, 1 MRT (D2Q9: Lallemand-Luo moments; D3Q19: d'Humieres), 2 TRT.
 // Each moving population changes by an increment built from its departure
-// from the rest equilibrium w_i rho; the rest population takes minus their
-// sum, so the node keeps its mass to the rounding of the stores.
+// from equilibrium; the rest population takes minus their sum, so the node
+// keeps its mass to the rounding of the stores.
 //
-// The velocity and force terms of Eqs. 2 and 11 are not formed population by
-// population.  SRT and TRT: over an opposite pair +-e, equilibrium less w rho is
-// w (e.u e.A - B) +- w e.U and the source w (e.u e.S - D) +- w e.V, with four
-// vectors and two scalars per component.  D2Q9 MRT: in its moments both are
-// polynomials of u and F.  The 2D step is partly bound by vector instructions, and
-// this takes about 110 per component instead of 260 for D2Q9 MRT, 22 per pair
-// instead of 26 for TRT.
-// Rates and source factors multiply a whole departure or source, formed first, as
-// Eq. 1 has it.  A rate that is multiplied into A, B and U beforehand (17 per pair)
-// is rounded there and exact on the populations; where tau is uniform that
-// mismatch has one sign at every node and step, and TRT's density error grew
-// 2.5 times in 100 steps of a 64 x 64 droplet at tau = 1, 2.9 times at 1.3.  This
-// form's, against forming each population by itself: TRT 0.84 to 0.95, SRT 0.92 to
-// 1.00 (tau 0.62 to 1.7, FP64 oracle); MRT 0.74 to 0.87.
+// SRT and TRT multiply the rate into a finished departure.  With the rate in the
+// equilibrium's coefficients beforehand (17 instructions per pair for 26) it is rounded
+// there and exact on the populations; where tau is uniform that mismatch has
+// one sign at every node and step, and after 100 steps of 64 x 64 droplets the
+// density error was 2.5 times this form's at tau = 1 and 2.9 times at 1.3 (TRT;
+// SRT up to 1.33).  Pair forms that keep the rate outside are as accurate as this
+// one and no faster (TRT up to 8 % slower: more vectors in registers).
 // ---------------------------------------------------------------------------
-template <int Q, int COLL, typename R>
+template <int Q, int COLL, int ST, typename R>
 __device__ __forceinline__ void collide_component(float (&fo)[Q], R rho, R ux, R uy, R uz, R Fx,
-                                                  R Fy, R Fz, const Rates<R> &r) {
-  using L = Lat<Q>;
-  const R uF = ux * Fx + uy * Fy + uz * Fz;
-  R moved = 0;  // sum of the moving populations' changes
-  if constexpr (COLL == 0 || COLL == 2) {
-    // even rate sp and odd rate sm (SRT: both s_nu), source factors 1 - s/2
-    const R sp = r.s_nu, sm = COLL == 0 ? r.s_nu : r.s_q;
-    const R fp = R(1) - R(0.5) * sp, fm = COLL == 0 ? fp : R(1) - R(0.5) * sm;
-    const R usq = ux * ux + uy * uy + uz * uz;
-    const R a = R(4.5) * rho, c = R(3) * rho;
-    const R Ax = a * ux, Ay = a * uy, Az = a * uz, Ux = c * ux, Uy = c * uy, Uz = c * uz;
-    const R Sx = R(9) * Fx, Sy = R(9) * Fy, Sz = R(9) * Fz, Vx = R(3) * Fx, Vy = R(3) * Fy, Vz = R(3) * Fz;
-    const R B = R(1.5) * rho * usq, D = R(3) * uF;
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-      const int o = L::opp[i];
-      if (o < i) continue;
-      const R eu = L::ex[i] * ux + L::ey[i] * uy + L::ez[i] * uz;
-      const R eA = L::ex[i] * Ax + L::ey[i] * Ay + L::ez[i] * Az;
-      const R eU = L::ex[i] * Ux + L::ey[i] * Uy + L::ez[i] * Uz;
-      const R eS = L::ex[i] * Sx + L::ey[i] * Sy + L::ez[i] * Sz;
-      const R eV = L::ex[i] * Vx + L::ey[i] * Vy + L::ez[i] * Vz;
-      const R w = (R)L::w[i];
-      const R q = fmar<R>(eu, eA, -B), s = fmar<R>(eu, eS, -D);
-      const R ai = fmar<R>(w, rho, -(R)fo[i]), ao = fmar<R>(w, rho, -(R)fo[o]);
-      if constexpr (COLL == 0) {
-        const R di = fmar<R>(sp, fmar<R>(w, q + eU, ai), fp * (w * (s + eV)));
-        const R dq = fmar<R>(sp, fmar<R>(w, q - eU, ao), fp * (w * (s - eV)));
-        fo[i] = (float)((R)fo[i] + di);
-        fo[o] = (float)((R)fo[o] + dq);
-        moved += di + dq;
-      } else {
-        const R dp = fmar<R>(sp, fmar<R>(w, q, R(0.5) * (ai + ao)), fp * (w * s));    // change of the symmetric part
-        const R dm = fmar<R>(sm, fmar<R>(w, eU, R(0.5) * (ai - ao)), fm * (w * eV));  // change of the antisymmetric part
-        fo[i] = (float)((R)fo[i] + (dp + dm));
-        fo[o] = (float)((R)fo[o] + (dp - dm));
-        moved = fmar<R>(R(2), dp, moved);
-      }
-    }
-  } else if constexpr (Q == 19) {
-    // MRT in the d'Humieres moments: the second-order moments relax at s_nu,
-    // e and eps at the free energy rates, pi at s_eps, j at s_j, q and m at
-    // s_q (equal even and odd rates give TRT, equal rates give SRT).
-    const R usq15 = R(1.5) * (ux * ux + uy * uy + uz * uz);
-    R dv[Q], S[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) departure<Q, R>(i, fo[i], rho, ux, uy, uz, Fx, Fy, Fz, usq15, uF, dv[i], S[i]);
-    auto rate = [&](int k) -> R {
-      switch (k) {
-        case 1: return r.s_e;
-        case 2: case 10: case 12: return r.s_eps;
-        case 3: case 5: case 7: return r.s_j;
-        case 4: case 6: case 8: case 16: case 17: case 18: return r.s_q;
-        default: return r.s_nu;
-      }
-    };
-    R dm[Q];
-#pragma unroll
-    for (int k = 1; k < Q; ++k) {
-      R a = 0, b = 0;
-#pragma unroll
-      for (int i = 0; i < Q; ++i) {
-        if (mrt19(k, i) != 0) {
-          a += R(mrt19(k, i)) * dv[i];
-          b += R(mrt19(k, i)) * S[i];
-        }
-      }
-      const R sk = rate(k);
-      dm[k] = (sk * a + (R(1) - R(0.5) * sk) * b) * (R(1) / R(mrt19_norm(k)));
-    }
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-      R v = 0;
-#pragma unroll
-      for (int k = 1; k < Q; ++k)
-        if (mrt19(k, i) != 0) v += R(mrt19(k, i)) * dm[k];
-      fo[i] = (float)((R)fo[i] + v);
-      moved += v;
-    }
-  } else {
-    // D2Q9 MRT in the Lallemand-Luo moments e, eps, jx, qx, jy, qy, pxx, pxy:
-    // moments of g = f - w rho, against those of the equilibrium at velocity u
-    // less its rest part, (3 u.u, -3 u.u, ux, -ux, uy, -uy, ux^2 - uy^2, ux uy) rho,
-    // and of the source, (6 u.F, -6 u.F, Fx, -Fx, Fy, -Fy, 2 (ux Fx - uy Fy),
-    // ux Fy + uy Fx)
-    R g[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) g[i] = fmar<R>(-(R)L::w[i], rho, (R)fo[i]);
-    const R s13 = g[1] + g[3], s24 = g[2] + g[4], s57 = g[5] + g[7], s68 = g[6] + g[8];
-    const R d13 = g[1] - g[3], d24 = g[2] - g[4], p5 = g[5] - g[7], p6 = g[6] - g[8];
-    const R ga = s13 + s24, gd = s57 + s68, pm = p5 - p6, pp = p5 + p6;
-    const R m_e = fmar<R>(R(2), gd, fmar<R>(R(-4), g[0], -ga));
-    const R m_eps = fmar<R>(R(-2), ga, fmar<R>(R(4), g[0], gd));
-    const R m_qx = fmar<R>(R(-2), d13, pm), m_qy = fmar<R>(R(-2), d24, pp);
-    const R rx = rho * ux, ry = rho * uy;
-    const R ruu = R(3) * fmar<R>(rx, ux, ry * uy), uF6 = R(6) * uF;
-    const R hj = R(1) - R(0.5) * r.s_j, hq = R(1) - R(0.5) * r.s_q, hn = R(1) - R(0.5) * r.s_nu;
-    // increments of the moments over their row norms, M^-1 = M^T diag(1/9,
-    // 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4)
-    const R ce = R(1.0 / 36.0) * fmar<R>(r.s_e, ruu - m_e, (R(1) - R(0.5) * r.s_e) * uF6);
-    const R cp = R(1.0 / 36.0) * fmar<R>(r.s_eps, -ruu - m_eps, -(R(1) - R(0.5) * r.s_eps) * uF6);
-    const R jx = R(1.0 / 6.0) * fmar<R>(r.s_j, rx - (d13 + pm), hj * Fx);
-    const R jy = R(1.0 / 6.0) * fmar<R>(r.s_j, ry - (d24 + pp), hj * Fy);
-    const R qx = R(1.0 / 12.0) * fmar<R>(r.s_q, -rx - m_qx, -hq * Fx);
-    const R qy = R(1.0 / 12.0) * fmar<R>(r.s_q, -ry - m_qy, -hq * Fy);
-    const R pxx = R(0.25) * fmar<R>(r.s_nu, fmar<R>(rx, ux, -ry * uy) - (s13 - s24),
-                                    R(2) * hn * fmar<R>(ux, Fx, -uy * Fy));
-    const R pxy = R(0.25) * fmar<R>(r.s_nu, fmar<R>(rx, uy, -(s57 - s68)), hn * fmar<R>(ux, Fy, uy * Fx));
-    const R ax = fmar<R>(R(-2), cp, -ce), dd = fmar<R>(R(2), ce, cp);
-    const R axp = ax + pxx, axm = ax - pxx, ddp = dd + pxy, ddm = dd - pxy;
-    const R X = fmar<R>(R(-2), qx, jx), Y = fmar<R>(R(-2), qy, jy), U = jx + qx, V = jy + qy;
-    const R df[Q] = {0, axp + X, axm + Y, axp - X, axm - Y, ddp + (U + V), ddm - (U - V), ddp - (U + V), ddm + (U - V)};
-#pragma unroll
-    for (int i = 1; i < Q; ++i) fo[i] = (float)((R)fo[i] + df[i]);
-    moved = R(4) * (ax + dd);  // the pairs' odd parts, pxx and pxy cancel in the sum
-  }
-  fo[0] = (float)((R)fo[0] - moved);
-}
-
-// The same collision with the equilibrium and the source formed population by
-// population (SRT, TRT and D2Q9 MRT), for BF16-deviation storage: the two forms
-// differ in the last FP32 place, which there decides BF16 roundings, and a
-// state held in 8 bits departs by 1e-5 within a hundred steps.  States in
-// that storage go on as they were begun, bit for bit.
-template <int Q, int COLL, typename R>
-__device__ __forceinline__ void collide_by_population(float (&fo)[Q], R rho, R ux, R uy, R uz, R Fx,
                                                   R Fy, R Fz, const Rates<R> &r) {
   using L = Lat<Q>;
   const R usq15 = R(1.5) * (ux * ux + uy * uy + uz * uz);
@@ -406,9 +273,88 @@ __device__ __forceinline__ void collide_by_population(float (&fo)[Q], R rho, R u
       fo[b] = (float)((R)fo[b] + (dp - dm));
       moved += R(2) * dp;
     }
+  } else if constexpr (Q == 19) {
+    // MRT in the d'Humieres moments: the second-order moments relax at s_nu,
+    // e and eps at the free energy rates, pi at s_eps, j at s_j, q and m at
+    // s_q (equal even and odd rates give TRT, equal rates give SRT).
+    R dv[Q], S[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) departure<Q, R>(i, fo[i], rho, ux, uy, uz, Fx, Fy, Fz, usq15, uF, dv[i], S[i]);
+    auto rate = [&](int k) -> R {
+      switch (k) {
+        case 1: return r.s_e;
+        case 2: case 10: case 12: return r.s_eps;
+        case 3: case 5: case 7: return r.s_j;
+        case 4: case 6: case 8: case 16: case 17: case 18: return r.s_q;
+        default: return r.s_nu;
+      }
+    };
+    R dm[Q];
+#pragma unroll
+    for (int k = 1; k < Q; ++k) {
+      R a = 0, b = 0;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        if (mrt19(k, i) != 0) {
+          a += R(mrt19(k, i)) * dv[i];
+          b += R(mrt19(k, i)) * S[i];
+        }
+      }
+      const R sk = rate(k);
+      dm[k] = (sk * a + (R(1) - R(0.5) * sk) * b) * (R(1) / R(mrt19_norm(k)));
+    }
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      R v = 0;
+#pragma unroll
+      for (int k = 1; k < Q; ++k)
+        if (mrt19(k, i) != 0) v += R(mrt19(k, i)) * dm[k];
+      fo[i] = (float)((R)fo[i] + v);
+      moved += v;
+    }
+  } else if constexpr (ST == 0) {
+    // D2Q9 MRT in the Lallemand-Luo moments e, eps, jx, qx, jy, qy, pxx, pxy:
+    // moments of g = f - w rho, against those of the equilibrium at velocity u
+    // less its rest part, (3 u.u, -3 u.u, ux, -ux, uy, -uy, ux^2 - uy^2, ux uy) rho,
+    // and of the source, (6 u.F, -6 u.F, Fx, -Fx, Fy, -Fy, 2 (ux Fx - uy Fy),
+    // ux Fy + uy Fx).  (About 110 vector instructions per component, and 0.74 to 0.87 of the density
+    // error, against 260 population by population: 1024 x 512 20.1 -> 17.0 us per step)
+    R g[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) g[i] = fmar<R>(-(R)L::w[i], rho, (R)fo[i]);
+    const R s13 = g[1] + g[3], s24 = g[2] + g[4], s57 = g[5] + g[7], s68 = g[6] + g[8];
+    const R d13 = g[1] - g[3], d24 = g[2] - g[4], p5 = g[5] - g[7], p6 = g[6] - g[8];
+    const R ga = s13 + s24, gd = s57 + s68, pm = p5 - p6, pp = p5 + p6;
+    const R m_e = fmar<R>(R(2), gd, fmar<R>(R(-4), g[0], -ga));
+    const R m_eps = fmar<R>(R(-2), ga, fmar<R>(R(4), g[0], gd));
+    const R m_qx = fmar<R>(R(-2), d13, pm), m_qy = fmar<R>(R(-2), d24, pp);
+    const R rx = rho * ux, ry = rho * uy;
+    const R ruu = R(3) * fmar<R>(rx, ux, ry * uy), uF6 = R(6) * uF;
+    const R hj = R(1) - R(0.5) * r.s_j, hq = R(1) - R(0.5) * r.s_q, hn = R(1) - R(0.5) * r.s_nu;
+    // increments of the moments over their row norms, M^-1 = M^T diag(1/9,
+    // 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4)
+    const R ce = R(1.0 / 36.0) * fmar<R>(r.s_e, ruu - m_e, (R(1) - R(0.5) * r.s_e) * uF6);
+    const R cp = R(1.0 / 36.0) * fmar<R>(r.s_eps, -ruu - m_eps, -(R(1) - R(0.5) * r.s_eps) * uF6);
+    const R jx = R(1.0 / 6.0) * fmar<R>(r.s_j, rx - (d13 + pm), hj * Fx);
+    const R jy = R(1.0 / 6.0) * fmar<R>(r.s_j, ry - (d24 + pp), hj * Fy);
+    const R qx = R(1.0 / 12.0) * fmar<R>(r.s_q, -rx - m_qx, -hq * Fx);
+    const R qy = R(1.0 / 12.0) * fmar<R>(r.s_q, -ry - m_qy, -hq * Fy);
+    const R pxx = R(0.25) * fmar<R>(r.s_nu, fmar<R>(rx, ux, -ry * uy) - (s13 - s24),
+                                    R(2) * hn * fmar<R>(ux, Fx, -uy * Fy));
+    const R pxy = R(0.25) * fmar<R>(r.s_nu, fmar<R>(rx, uy, -(s57 - s68)), hn * fmar<R>(ux, Fy, uy * Fx));
+    const R ax = fmar<R>(R(-2), cp, -ce), dd = fmar<R>(R(2), ce, cp);
+    const R axp = ax + pxx, axm = ax - pxx, ddp = dd + pxy, ddm = dd - pxy;
+    const R X = fmar<R>(R(-2), qx, jx), Y = fmar<R>(R(-2), qy, jy), U = jx + qx, V = jy + qy;
+    const R df[Q] = {0, axp + X, axm + Y, axp - X, axm - Y, ddp + (U + V), ddm - (U - V), ddp - (U + V), ddm + (U - V)};
+#pragma unroll
+    for (int i = 1; i < Q; ++i) fo[i] = (float)((R)fo[i] + df[i]);
+    moved = R(4) * (ax + dd);  // the pairs' odd parts, pxx and pxy cancel in the sum
   } else {
-    // D2Q9 MRT: moments (Lallemand-Luo rows e, eps, jx, qx, jy, qy, pxx,
-    // pxy) of the departures from equilibrium and of the source
+    // D2Q9 MRT with BF16-deviation storage, population by population: the two forms
+    // differ in the last FP32 place, which there decides BF16 roundings, and a state
+    // held in 8 bits departs by 1e-5 within a hundred steps.  Moments (Lallemand-Luo
+    // rows e, eps, jx, qx, jy, qy, pxx, pxy) of the departures from equilibrium and
+    // of the source
     R d[Q], S[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) departure<Q, R>(i, fo[i], rho, ux, uy, uz, Fx, Fy, Fz, usq15, uF, d[i], S[i]);
@@ -484,13 +430,8 @@ __device__ __forceinline__ void collide_node(const InstDev &d, float (&f0)[Q], f
   const R uy = (jy + h * (F1y + F2y)) * inv_rho;
   const R uz = (jz + h * (F1z + F2z)) * inv_rho;
   const Rates<R> r = node_rates<R>(d, rho1, rho2, inv_rho);
-  if constexpr (ST == 1 && !(Q == 19 && COLL == 1)) {
-    collide_by_population<Q, COLL, R>(f0, rho1, ux, uy, uz, F1x, F1y, F1z, r);
-    collide_by_population<Q, COLL, R>(f1, rho2, ux, uy, uz, F2x, F2y, F2z, r);
-  } else {
-    collide_component<Q, COLL, R>(f0, rho1, ux, uy, uz, F1x, F1y, F1z, r);
-    collide_component<Q, COLL, R>(f1, rho2, ux, uy, uz, F2x, F2y, F2z, r);
-  }
+  collide_component<Q, COLL, ST, R>(f0, rho1, ux, uy, uz, F1x, F1y, F1z, r);
+  collide_component<Q, COLL, ST, R>(f1, rho2, ux, uy, uz, F2x, F2y, F2z, r);
 }
 
 // ---------------------------------------------------------------------------
