@@ -669,8 +669,8 @@ lbm_status create_batch(int32_t k, const lbm_geometry *g, const lbm_params *p,
   b->compact = compact_strategy(strategy);
   int64_t tiles = 0;
   for (int i = 0; i < k; ++i) tiles += (int64_t)((g[i].nx + kTileX - 1) / kTileX) * ((g[i].ny + 7) / 8);
-  const lbm_status ps =
-      apply_plan(b, strategy, p[0].tile_rows ? p[0].tile_rows : fused_rows(b->storage, b->compact, tiles));
+  const int default_rows = fused_rows(b->storage, b->math == LBM_MATH_F64, b->compact, tiles);
+  const lbm_status ps = apply_plan(b, strategy, p[0].tile_rows ? p[0].tile_rows : default_rows);
   if (ps != LBM_OK) return ps;
   *out = owner.release();
   return LBM_OK;
@@ -1057,7 +1057,8 @@ lbm_status lbm_batch_kernel_info(const lbm_batch *b, char *name, size_t name_len
   if (block_threads) {
     const bool fused9 = b->q == 9 && (b->strategy == LBM_FUSED || b->strategy == LBM_COMPACT_FUSED);
     *block_threads = b->strategy == LBM_COMPACT ? kCompactThreads
-                     : fused9 ? 64 * fused_waves(b->ty, b->math == LBM_MATH_F64, b->storage, b->compact)
+                     : fused9 ? 64 * fused_waves(b->ty, b->collision, b->math == LBM_MATH_F64, b->storage, b->compact,
+                                                  b->n_blocks)
                               : 256;
   }
   return LBM_OK;

@@ -20,18 +20,31 @@ constexpr uint32_t kLinkMask = (1u << 19) - 1u;
 // 2D step tile: 64 lanes cover 60 interior columns plus 2 halo columns on
 // each side; TY interior rows (8, 12 or 16) plus 2 halo rows above and below.
 constexpr int kTileX = 60;
-// Waves per block of the fused D2Q9 step (lbm_step.h has the measurements).
-constexpr int fused_waves(int ty, bool f64, int storage, bool compact) {
-  return ty == 8 && !(compact && !(f64 && storage == LBM_STORE_F32)) ? 8 : 4;
+// Waves per block of the fused D2Q9 step: four, or eight with a row each for the 8-row
+// tile while waves are what is short (tiles: blocks of the launch, of 60 x 8 nodes; collision: as in
+// lbm.h).  us per step with four / eight waves:
+//   dense FP32: 182 tiles 8.9 / 7.8, 4250 73.0 / 70.7, 9400 152.2 / 154.2, 25125 390 / 404;
+//   dense FP64: 500 tiles 15.0 / 13.4, 1152 18.1 / 21.1, 9400 150 / 156;
+//   dense BF16: 500 tiles 16.1 / 14.2, 1152 22.3 / 22.2, 1350 24.6 / 25.3, 4250 54.4 / 61.6
+//     (MRT in FP64, of 256 registers with two rows: 1152 33.1 / 28.5, 25125 766 / 555);
+//   compacted FP64: 500 tiles 20.2 / 17.5, 2125 40.4 / 40.0, 4250 66.9 / 71.3.
+// The compacted FP32 and BF16 steps: lbm_step.h.
+constexpr int fused_waves(int ty, int collision, bool f64, int storage, bool compact, int64_t tiles) {
+  const bool bf16 = storage != LBM_STORE_F32;
+  if (ty != 8 || (compact && (!f64 || bf16))) return 4;
+  if (bf16 && f64 && collision == 1) return 8;
+  return tiles <= (compact ? 3000 : bf16 ? 1280 : f64 ? 1024 : 6000) ? 8 : 4;
 }
 // Tile height of the fused D2Q9 step when none is asked for (tiles: of 60 x 8 nodes,
-// all instances).  8 rows, but 12 with BF16 storage, whose pulls are the dearest
-// per halo row, where waves are not what is short: on the compacted layout (24
+// all instances).  8 rows, but 12 where the pulls are the dearest per halo row and
+// waves are not what is short.  With BF16 storage: on the compacted layout (24
 // uneven instances: 109 us per step against 114 with 8), and on the dense one above
 // five tiles per CU (2648 tiles: 43 us against 47 with 8; 1472: 28 and 30;
-// 1064: 27 and 24; 24: 23 and 8.5).
-constexpr int fused_rows(int storage, bool compact, int64_t tiles) {
-  return storage != LBM_STORE_F32 && (compact || tiles > 1280) ? 12 : 8;
+// 1064: 27 and 24; 24: 23 and 8.5).  With FP64 arithmetic on the compacted layout above
+// 3000 tiles (9400: 145 us against 152 with 8; 4250: 66.6 and 66.9; 2125: 41.9 and 41.2).
+constexpr int fused_rows(int storage, bool f64, bool compact, int64_t tiles) {
+  const bool bf16 = storage != LBM_STORE_F32;
+  return (bf16 && (compact || tiles > 1280)) || (f64 && compact && tiles > 3000) ? 12 : 8;
 }
 // 3D step tile: the same 64-lane rows, TY3 interior rows in y, marching in z.
 constexpr int kTileY3 = 8;

@@ -454,32 +454,30 @@ __device__ __forceinline__ void ccomplete9(const InstDev &d, gcf *__restrict__ f
 // 1024 x 512 20.1 / 20.8 (23.8), 2000 x 1000 70.4 / 76.0 (75.0), nine
 // 192 x 192 droplets 12.6 / 13.4 (15.3).  The compacted FP32 step keeps four
 // waves (24 uneven instances: 104.9 against 115.1 us): its rank lookups cost
-// more per row than the registers of a second row; in FP64 eight win there
-// too (165 against 188-196).
-// (With the collision's algebra per opposite pair, since then: 1024 x 512 17.0,
+// more per row than the registers of a second row; in FP64 eight win there up
+// to 3000 tiles.
+// (With the MRT collision's algebra in moments, since then: 1024 x 512 17.0,
 // 24 uneven instances 101.5.)
 // Four waves with TY = 12, and with TY = 8 in FP32, park the last interior row of
 // each wave in LDS between the phases, to fit four and six waves per SIMD.
-template <int TY, typename R, int ST, int CL> struct FusedShape {
+template <int TY, typename R, int ST, int NW> struct FusedShape {
   static constexpr bool kF32 = sizeof(R) == 4 && ST == 0;
-  static constexpr int kNW = fused_waves(TY, sizeof(R) == 8, ST, CL);  // waves per block
-  static constexpr int kRows = TY / kNW;                               // interior rows per wave
+  static constexpr int kRows = TY / NW;  // interior rows per wave
   static constexpr int kParked = (kRows == 3 || (kRows == 2 && kF32)) ? 1 : 0;  // of them kept in LDS
   static constexpr int kWaves = kRows == 4 ? 1 : ((kRows <= 2 && kF32) ? 6 : 4);
 };
 
 // CL = 1: the same step over the compacted layout (fluid nodes only stored,
 // pulls by rank, bounce-back from the node's own slots, no ghost slots).
-template <int COLL, int ST, typename R, int TY, int CL = 0>
-__global__ __launch_bounds__((64 * FusedShape<TY, R, ST, CL>::kNW))
-    __attribute__((amdgpu_waves_per_eu(FusedShape<TY, R, ST, CL>::kWaves))) void step_d2q9(
+template <int COLL, int ST, typename R, int TY, int CL, int NW>
+__global__ __launch_bounds__(64 * NW)
+    __attribute__((amdgpu_waves_per_eu(FusedShape<TY, R, ST, NW>::kWaves))) void step_d2q9(
     const InstDev *__restrict__ insts, const int32_t *__restrict__ block_inst, int parity) {
   using L = Lat<9>;
   using V = Vec2<R>;
-  constexpr int NW = FusedShape<TY, R, ST, CL>::kNW;
   constexpr int KR = TY / NW;       // interior rows per wave
   constexpr int kRH = TY + 4;       // region rows
-  constexpr int KP = FusedShape<TY, R, ST, CL>::kParked;
+  constexpr int KP = FusedShape<TY, R, ST, NW>::kParked;
   __shared__ V psi[kRH][64];
   __shared__ float park[KP > 0 ? KP * NW : 1][18][64];  // [row slot * NW + wave][component * 9 + link][lane]
 
@@ -1787,21 +1785,35 @@ __global__ __launch_bounds__(256) void fwd_ivsd_kernel(const InstDev *__restrict
   psi[key] = v2f{(float)(d.chi1 * s1 * inv), (float)(d.chi2 * s2 * inv)};
 }
 
+template <int COLL, int ST, typename R, int CL>
+static void launch_fused9(int ty, const InstDev *d, const int32_t *bi, int64_t nb, int parity, hipStream_t s) {
+  const dim3 g((unsigned)nb);
+  constexpr bool kF64 = sizeof(R) == 8;
+  if (ty == 16) {
+    step_d2q9<COLL, ST, R, 16, CL, 4><<<g, 256, 0, s>>>(d, bi, parity);
+    return;
+  }
+  if (ty != 8) {
+    step_d2q9<COLL, ST, R, 12, CL, 4><<<g, 256, 0, s>>>(d, bi, parity);
+    return;
+  }
+  // (the waves at the smallest and the largest launch: forms the rule never asks for are not built)
+  if constexpr (fused_waves(8, COLL, kF64, ST, CL, 0) == 8) {
+    if (fused_waves(8, COLL, kF64, ST, CL, nb) == 8) {
+      step_d2q9<COLL, ST, R, 8, CL, 8><<<g, 512, 0, s>>>(d, bi, parity);
+      return;
+    }
+  }
+  if constexpr (fused_waves(8, COLL, kF64, ST, CL, INT64_MAX) == 4) step_d2q9<COLL, ST, R, 8, CL, 4><<<g, 256, 0, s>>>(d, bi, parity);
+}
+
 template <int COLL, int ST, typename R>
 static void launch_fused_q(int q, int ty, const InstDev *d, const int32_t *bi, int64_t nb, int parity,
                            hipStream_t s, bool compact = false) {
   const dim3 g((unsigned)nb), b(256);
   if (q == 9) {
-    const dim3 bt(64 * fused_waves(ty, sizeof(R) == 8, ST, compact));
-    if (compact) {
-      if (ty == 8) step_d2q9<COLL, ST, R, 8, 1><<<g, bt, 0, s>>>(d, bi, parity);
-      else if (ty == 16) step_d2q9<COLL, ST, R, 16, 1><<<g, bt, 0, s>>>(d, bi, parity);
-      else step_d2q9<COLL, ST, R, 12, 1><<<g, bt, 0, s>>>(d, bi, parity);
-    } else {
-      if (ty == 8) step_d2q9<COLL, ST, R, 8><<<g, bt, 0, s>>>(d, bi, parity);
-      else if (ty == 16) step_d2q9<COLL, ST, R, 16><<<g, bt, 0, s>>>(d, bi, parity);
-      else step_d2q9<COLL, ST, R, 12><<<g, bt, 0, s>>>(d, bi, parity);
-    }
+    if (compact) launch_fused9<COLL, ST, R, 1>(ty, d, bi, nb, parity, s);
+    else launch_fused9<COLL, ST, R, 0>(ty, d, bi, nb, parity, s);
   } else {
     step_d3q19<COLL, ST, R><<<g, b, 0, s>>>(d, bi, parity);
   }
