@@ -213,26 +213,30 @@ __global__ __launch_bounds__(256) void igemm_fwd(GemmArgs a) {
 // outside the image) and the group's weights of its output channels in LDS
 // once, and all nine taps of all four waves read their MFMA fragments from
 // there.  Wave tile TM x TN MFMA tiles (32 x 32 each); the four waves are
-// stacked along the pixels, so a block covers 256 consecutive pixels --
+// stacked along the pixels, so a block covers 128 TM consecutive pixels --
 // whole image rows (16 <= w <= 256, w divides the block, h * w a multiple of
-// it) -- and 64 output channels.  Needs the reduction channels to be a
+// it) -- and 32 TN output channels.  Needs the reduction channels to be a
 // multiple of 16.  For images 16 columns wide and outputs that cannot be stored as
-// vectors; the rest goes to conv3x3_rows.
+// vectors; the rest goes to conv3x3_rows.  512 pixels by 32 channels for outputs of
+// at most 32 channels once there is such a block per CU, 256 by 64 otherwise (us,
+// 512 x 32 / 256 x 64: 32 -> 12 at 16 x 128 x 128 13.5 / 18.2, 64 -> 32 at 512 x 32 x 16
+// 20.5 / 28.0; 64 -> 20 at two 256 x 256 images, 256 blocks, 24.7 / 29.9; 32 -> 12
+// at 64 x 32 x 32, 128 blocks, 10.5 / 8.2).
 // ---------------------------------------------------------------------------
-constexpr int kConvBlockPix = 256;
 // largest staged region over the allowed widths: (pixels / w + 2) rows of w + 2
-constexpr int conv_halo_pix() {
+constexpr int conv_halo_pix(int block_pix) {
   int m = 0;
   for (int w = 16; w <= 256; w *= 2) {
-    const int v = (kConvBlockPix / w + 2) * (w + 2);
+    const int v = (block_pix / w + 2) * (w + 2);
     m = v > m ? v : m;
   }
   return m;
 }
 
+template <int TM, int TN>
 __global__ __launch_bounds__(256) void conv3x3_lds(GemmArgs a) {
-  constexpr int TM = 2, TN = 2, BP = kConvBlockPix, BC = 32 * TN;
-  __shared__ uint4 sA[conv_halo_pix() * 2];  // [region pixel][channel half of the group]
+  constexpr int BP = 128 * TM, BC = 32 * TN;
+  __shared__ uint4 sA[conv_halo_pix(BP) * 2];  // [region pixel][channel half of the group]
   __shared__ uint4 sB[BC * 9 * 2];             // [output channel][tap][channel half]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5;
@@ -260,7 +264,7 @@ __global__ __launch_bounds__(256) void conv3x3_lds(GemmArgs a) {
   // loads go to registers before this group's taps run, and are parked in
   // LDS after the barrier that ends them.  Each thread's staged elements
   // keep their place from group to group; only the channel offset moves.
-  constexpr int KA = (conv_halo_pix() * 2 + 255) / 256, KB = (BC * 9 * 2 + 255) / 256;
+  constexpr int KA = (conv_halo_pix(BP) * 2 + 255) / 256, KB = (BC * 9 * 2 + 255) / 256;
   const int nA = rows * rw * 2;
   constexpr uint32_t kNone = 0xffffffffu;  // element outside the image or the weights
   uint32_t offA[KA], offB[KB];              // element offsets (host keeps them below 2^32 - 1)
@@ -335,9 +339,8 @@ __global__ __launch_bounds__(256) void conv3x3_lds(GemmArgs a) {
   }
 }
 
-// Can the LDS-staged kernel run this convolution?
-static bool conv_lds_fits(const GemmArgs &a) {
-  const int bp = kConvBlockPix;
+// Can the LDS-staged kernel with blocks of bp pixels run this convolution?
+static bool conv_lds_fits(const GemmArgs &a, int bp) {
   // element offsets of the input and the weights must fit 32 bits
   const bool small = (int64_t)a.n * a.h * a.w * a.x_cs < ((int64_t)1 << 32) - 1 &&
                      (int64_t)a.nout * 9 * a.kc < ((int64_t)1 << 32) - 1;
@@ -908,7 +911,7 @@ static int64_t conv_rows_tiles(const GemmArgs &a, int bc) {
 }
 static bool conv_rows_fits(const GemmArgs &a, int64_t P) {
   const int64_t rows = a.w < 128 ? kConvTilePix / a.w + 2 : kConvTilePix / 128 + 2;
-  return a.w >= 32 && conv_lds_fits(a) && direct_fits(a, P, 9) && rows * a.w * a.x_cs * 2 < kWholeBuffer;
+  return a.w >= 32 && conv_lds_fits(a, 256) && direct_fits(a, P, 9) && rows * a.w * a.x_cs * 2 < kWholeBuffer;
 }
 
 template <int TN>
@@ -937,13 +940,14 @@ static bool launch_conv3x3(const GemmArgs &a, int64_t P, hipStream_t s) {
   } else if (conv_rows_fits(a, P) && conv_rows_tiles(a, 32) >= (a.kc > 32 ? 64 : 192)) {
     if (a.nout > 32 && conv_rows_tiles(a, 64) >= 256) launch_conv_rows<2>(a, s);
     else launch_conv_rows<1>(a, s);
-  } else if (conv_lds_fits(a)) {
+  } else if (conv_lds_fits(a, 256)) {
     // sixteen columns wide, or too few tiles, or outputs that are not whole
     // vectors: 64 blocks of the staged kernel leave most CUs idle
-    const dim3 g((unsigned)(P / kConvBlockPix), (unsigned)((a.nout + 63) / 64));
+    const dim3 g((unsigned)(P / 256), (unsigned)((a.nout + 63) / 64));
     if (direct && (a.w >= 32 || (int64_t)g.x * g.y <= 64)) launch_direct_tiles<0>(a, P, s);
     else {
-      conv3x3_lds<<<g, 256, 0, s>>>(a);
+      if (a.nout <= 32 && P >= 256 * 512 && conv_lds_fits(a, 512)) conv3x3_lds<4, 1><<<(unsigned)(P / 512), 256, 0, s>>>(a);
+      else conv3x3_lds<2, 2><<<g, 256, 0, s>>>(a);
       return false;
     }
   } else if (direct && a.kc % 16 == 0) {
