@@ -980,6 +980,163 @@ struct WgradArgs {
 };
 
 // ---------------------------------------------------------------------------
+// Weight gradients by gathered pixels, for the grids where whole rows or 16-column
+// segments leave the kernels below little to work on.  A block sums its 4096
+// pixels for one tile of (output channel, tap and input channel); MODE 1 has a block per
+// tap.  Per stage of 128 pixels in memory order, whatever the width, each thread
+// loads an 8-pixel x 8-channel block of one operand (eight 16-byte vectors),
+// transposes it in registers (byte permutes) and writes it channel-major to LDS, so
+// an MFMA operand fragment (8 consecutive pixels of one channel) is one 128-bit
+// LDS read and neither side of LDS sees bank conflicts.
+// ---------------------------------------------------------------------------
+constexpr int kStagePix = 128;  // pixels per LDS stage
+constexpr int kStageLd = kStagePix + 8;
+
+// 8 x 8 transpose of 16-bit values: in[p] holds channels 0..7 of pixel p,
+// out[c] receives pixels 0..7 of channel c.
+__device__ __forceinline__ void transpose8x8(const uint4 (&in)[8], uint4 (&out)[8]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t lo[4], hi[4];  // channel 2j and 2j + 1, pixel pairs i
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t a = (&in[2 * i].x)[j], b = (&in[2 * i + 1].x)[j];
+      lo[i] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+      hi[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+    }
+    out[2 * j] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    out[2 * j + 1] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+  }
+}
+
+// Block tile (32 MT) x (32 NT) of C with MT * NT = 4 waves, each one 32 x 32
+// MFMA tile: (2, 2) in general, (1, 4) when the output channels fit 32.
+template <int MODE, int MT, int NT>
+__global__ __launch_bounds__(256) void wgrad_gather(WgradArgs a) {
+  static_assert(MT * NT == 4, "four waves");
+  __shared__ __attribute__((aligned(16))) uint16_t sA[32 * MT][kStageLd];  // [m][pixel]
+  __shared__ __attribute__((aligned(16))) uint16_t sB[32 * NT][kStageLd];  // [n][pixel]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave % MT, wn = wave / MT;
+  const int half = lane >> 5;
+  const int64_t P = (int64_t)a.n * a.h * a.w;
+  const int64_t p_begin = (int64_t)blockIdx.x * kWgradPix;
+  const int m0 = blockIdx.y * 32 * MT;  // output channel block
+  const int tapz = MODE == 1 ? (int)(blockIdx.z % 4) : 0;
+  const int nblk = MODE == 1 ? (int)(blockIdx.z / 4) : (int)blockIdx.z;
+  const int n0 = nblk * 32 * NT;        // column block
+  floatx16 acc = {};
+  // the blocks of the first column block also sum dy over their pixels (bias)
+  const bool bias_blk = a.bpartial && nblk == 0 && tid < 32 * MT;
+  float bacc = 0.f;
+  const int64_t p_end = p_begin + kWgradPix < P ? p_begin + kWgradPix : P;
+  // staging: 8-pixel x 8-channel blocks, 64 MT of A then 64 NT of B; a
+  // thread owns entries tid and tid + 256.  The next stage's loads go to
+  // registers before this stage's products run; the transpose and the LDS
+  // stores follow the barrier that ends them.
+  constexpr int kEntries = 64 * (MT + NT), NE = (kEntries + 255) / 256;
+  uint4 v[NE][8];
+  auto load_stage = [&](int64_t pcs) {
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+      const int e = tid + 256 * j;
+      const bool stage_b = e >= 64 * MT;
+      const int eo = stage_b ? e - 64 * MT : e;
+      const int cg = eo >> 4, pb = eo & 15;
+      // image, row and column of the first of the 8 consecutive pixels; the
+      // others follow by increments (wrapping at row and image ends)
+      const int64_t pfirst = pcs + pb * 8;
+      int pn = (int)(pfirst / ((int64_t)a.h * a.w));
+      const int rr0 = (int)(pfirst - (int64_t)pn * a.h * a.w);
+      int py = rr0 / a.w, px = rr0 - py * a.w;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const int64_t p = pfirst + r;
+        if (r > 0 && ++px == a.w) {
+          px = 0;
+          if (++py == a.h) {
+            py = 0;
+            ++pn;
+          }
+        }
+        v[j][r] = make_uint4(0, 0, 0, 0);
+        if (e >= kEntries || p >= p_end) continue;
+        if (!stage_b) {
+          const int m = m0 + cg * 8;
+          if (m < a.cout) {
+            int64_t q;
+            if constexpr (MODE == 0) {
+              q = p;
+            } else {
+              const int H2 = 2 * a.h, W2 = 2 * a.w;
+              q = (int64_t)pn * H2 * W2 + (int64_t)(2 * py + (tapz >> 1)) * W2 + 2 * px + (tapz & 1);
+            }
+            v[j][r] = *reinterpret_cast<const uint4 *>(a.dy + q * a.dy_cs + a.dy_co + m);
+          }
+        } else {
+          const int nn = n0 + cg * 8;
+          if (nn < a.ncol) {
+            if constexpr (MODE == 0) {
+              const int tap = nn / a.cin, ci = nn - tap * a.cin;
+              const int yy = py + tap / 3 - 1, xx = px + tap % 3 - 1;
+              if (yy >= 0 && yy < a.h && xx >= 0 && xx < a.w)
+                v[j][r] = *reinterpret_cast<const uint4 *>(
+                    a.x + ((int64_t)pn * a.h * a.w + (int64_t)yy * a.w + xx) * a.x_cs + a.x_co + ci);
+            } else {
+              v[j][r] = *reinterpret_cast<const uint4 *>(a.x + p * a.x_cs + a.x_co + nn);
+            }
+          }
+        }
+      }
+    }
+  };
+  if (p_begin < p_end) load_stage(p_begin);
+  for (int64_t pc = p_begin; pc < p_end; pc += kStagePix) {
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+      const int e = tid + 256 * j;
+      if (e >= kEntries) continue;
+      const bool stage_b = e >= 64 * MT;
+      const int eo = stage_b ? e - 64 * MT : e;
+      const int cg = eo >> 4, pb = eo & 15;
+      uint4 t[8];
+      transpose8x8(v[j], t);
+      uint16_t(*dst)[kStageLd] = stage_b ? sB : sA;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) *reinterpret_cast<uint4 *>(&dst[cg * 8 + c][pb * 8]) = t[c];
+    }
+    __syncthreads();
+    if (pc + kStagePix < p_end) load_stage(pc + kStagePix);
+    if (bias_blk) {
+#pragma unroll
+      for (int q = 0; q < kStagePix; q += 8) {
+        const uint4 u = *reinterpret_cast<const uint4 *>(&sA[tid][q]);
+        const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bacc += bf2f((uint16_t)(w4[k] & 0xffffu)) + bf2f((uint16_t)(w4[k] >> 16));
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < kStagePix; ks += 16) {
+      const uint4 av = *reinterpret_cast<const uint4 *>(&sA[wm * 32 + (lane & 31)][ks + 8 * half]);
+      const uint4 bv = *reinterpret_cast<const uint4 *>(&sB[wn * 32 + (lane & 31)][ks + 8 * half]);
+      acc = mfma(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), acc);
+    }
+    __syncthreads();
+  }
+  const int ntap = MODE == 1 ? 4 : 1;
+  if (bias_blk && m0 + tid < a.cout)
+    a.bpartial[((int64_t)blockIdx.x * ntap + tapz) * a.cout + m0 + tid] = bacc;
+  const int nn = n0 + wn * 32 + (lane & 31);
+  if (nn >= a.ncol) return;
+  float *out = a.partial + ((int64_t)blockIdx.x * ntap + tapz) * (int64_t)a.cout * a.ncol;
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm * 32 + c_row(r, lane);
+    if (m < a.cout) out[(int64_t)m * a.ncol + nn] = acc[r];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Weight gradients with all taps in one wave, for images of any width.  A wave owns a 32 x 32 tile of
 // (output, input) channels and marches down image rows, 16 pixels of a row
 // at a time, accumulating every tap of that tile: a row of x enters three
@@ -1562,6 +1719,47 @@ static void launch_wgrad_taps(const WgradArgs &a, int kb, hipStream_t s) {
   const int64_t per_wave = (total + 8 * (int64_t)kb - 1) / (8 * (int64_t)kb);
   const int ci_tiles = (a.cin + 31) / 32, tiles = ci_tiles * ((a.cout + 31) / 32);
   wgrad_taps<MODE><<<wg_grid(kb, tiles), kWgThreads, 0, s>>>(a, kb, per_wave, ci_tiles, tiles);
+}
+
+template <int MODE>
+static void launch_wgrad_gather(const WgradArgs &a, int kb, hipStream_t s) {
+  const unsigned taps = MODE == 1 ? 4 : 1;
+  if (a.cout <= 32) {
+    wgrad_gather<MODE, 1, 4><<<dim3((unsigned)kb, 1, taps * (unsigned)((a.ncol + 127) / 128)), 256, 0, s>>>(a);
+  } else {
+    const dim3 g((unsigned)kb, (unsigned)((a.cout + 63) / 64), taps * (unsigned)((a.ncol + 63) / 64));
+    wgrad_gather<MODE, 2, 2><<<g, 256, 0, s>>>(a);
+  }
+}
+
+// The kernel of a weight gradient, by measurement over 4493 (MODE 1: 4294) shapes from
+// 1 x 1 x 1 to 16 x 300 x 300 pixels and 8 to 1024 channels.  wgrad_gather where
+//   - a stage or two of its 128 pixels is all there is (us, it / the other, 64 -> 64: 1 x 5 x 17
+//     10.6 / 12.8; 1 x 16 x 16 12.5 / 11.8 in MODE 0);
+//   - images have few columns: a 16-column segment is mostly empty (64 -> 64: 16 x 1000 x 1
+//     85 / 258, 16 x 300 x 2 84 / 111, 1 x 300 x 3 26.5 / 30.6, 1 x 300 x 4 31.0 / 30.6, MODE 1
+//     31.1 / 35.9; MODE 1, 256 -> 256: 16 x 300 x 8 99 / 139), the more so the fuller the chip;
+//   - MODE 1 fills it with blocks that waste a quarter of a stage (256 -> 256 at 16 x 32 x 96
+//     103 / 134; with fewer shares not: 512 -> 512 at 2 x 48 x 48 90 / 51) or read dy eight times
+//     as wide as x (64 -> 1024 at 16 x 33 x 100 162 / 211).
+template <int MODE>
+static bool gather_wins(const WgradArgs &a, int kb, bool rows) {
+  const int64_t P = (int64_t)a.n * a.h * a.w, tiles = (int64_t)((a.cin + 31) / 32) * ((a.cout + 31) / 32);
+  const int64_t blocks = kb * tiles;
+  if (rows) return MODE == 0 ? P <= 128 : kb >= 3 && blocks >= 512 && 128 / a.w * a.w <= 96;
+  if (P <= 128 || (P <= 256 && (a.cout > 32 || a.w <= 8))) return true;
+  if (MODE == 0) return a.w <= 2 || (a.w == 3 && a.cout > 32) || (a.w <= 4 && P <= 1024);
+  return a.w <= 4 || (a.w <= 6 && (P <= 512 || blocks >= 256)) || (a.w <= 12 && kb >= 3 && blocks >= 512) ||
+         (blocks >= 512 && a.cout >= 8 * a.cin) || (tiles >= 1024 && P <= 2048);
+}
+
+template <int MODE>
+static void launch_wgrad(const WgradArgs &a, int kb, hipStream_t s) {
+  constexpr int SP = MODE == 0 ? 256 : 128;
+  const bool rows = wgrad_rows_fits(a, SP);
+  if (gather_wins<MODE>(a, kb, rows)) launch_wgrad_gather<MODE>(a, kb, s);
+  else if (rows) launch_wgrad_rows<MODE, SP>(a, kb, s);
+  else launch_wgrad_taps<MODE>(a, kb, s);
 }
 
 // sum_{k < count} p[k * stride] in a fixed order: eight interleaved partial
@@ -2174,8 +2372,7 @@ int unet_conv3x3_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs
   const int kb = (int)((P + kWgradPix - 1) / kWgradPix);
   const int64_t wpart = (int64_t)kb * cout * 9 * cin;
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, 9 * cin, db ? partial + wpart : nullptr};
-  if (wgrad_rows_fits(a, 256)) launch_wgrad_rows<0, 256>(a, kb, (hipStream_t)s);
-  else launch_wgrad_taps<0>(a, kb, (hipStream_t)s);
+  launch_wgrad<0>(a, kb, (hipStream_t)s);
   launch_wgrad_reduce(partial, kb, 1, cout, 9 * cin, dw, accumulate, partial + wpart, kb, db, (hipStream_t)s);
   return launched();
 }
@@ -2300,8 +2497,7 @@ int unet_upconv_wgrad(const uint16_t *x, int n, int h, int w, int cin, int x_cs,
   const int kb = (int)((P + kWgradPix - 1) / kWgradPix);
   const int64_t wpart = (int64_t)kb * 4 * cout * cin;
   WgradArgs a{x, n, h, w, cin, x_cs, x_co, dy, cout, dy_cs, dy_co, partial, cin, db ? partial + wpart : nullptr};
-  if (wgrad_rows_fits(a, 128)) launch_wgrad_rows<1, 128>(a, kb, (hipStream_t)s);
-  else launch_wgrad_taps<1>(a, kb, (hipStream_t)s);
+  launch_wgrad<1>(a, kb, (hipStream_t)s);
   launch_wgrad_reduce(partial, kb, 4, cout, cin, dw, 0, partial + wpart, (int64_t)kb * 4, db, (hipStream_t)s);
   return launched();
 }
