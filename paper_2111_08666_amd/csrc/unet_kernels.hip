@@ -2523,8 +2523,8 @@ static int head_loss_bwd(const uint16_t *x, int n_pix, int c, int x_cs, const fl
   float *g = partial, *l = partial + n_pix, *sums = partial + 2 * (int64_t)n_pix;
   const int blocks = (int)(((int64_t)n_pix + kHeadPix - 1) / kHeadPix);
   if (c <= 64 && vec8(x, c, x_cs, 0) && (!dx || vec8(dx, c, c, 0)))
-    head_loss_pix_v<<<(n_pix + 255) / 256, 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, w, b, target, mask, scale, dx, g,
-                                                                     l, relu);
+    head_loss_pix_v<<<(unsigned)(((int64_t)n_pix + 255) / 256), 256, 0, (hipStream_t)s>>>(
+        x, n_pix, c, x_cs, w, b, target, mask, scale, dx, g, l, relu);
   else {
     head_loss_pix<<<grid1d(n_pix), 256, 0, (hipStream_t)s>>>(x, n_pix, c, x_cs, w, b, target, mask, scale, dx, g, l);
     if (relu && dx) launch_relu_bwd(x, n_pix, c, x_cs, 0, dx, c, 0, (hipStream_t)s);
