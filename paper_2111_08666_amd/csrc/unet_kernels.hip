@@ -1178,6 +1178,15 @@ template <int MODE> __host__ __device__ inline int64_t wg_rows(const WgradArgs &
   return (int64_t)a.n * (MODE == 0 ? a.h + 1 : a.h);
 }
 
+// Between a wave's LDS writes and other lanes' reads of them, and back: LDS operations of
+// a wave are done in order, so no wait is needed, only that the compiler keeps
+// the order (it sees one lane, whose addresses need not meet).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block -> (share of the pixels, channel tile), tiles fastest: each XCD takes a
 // contiguous range (blocks go round the XCDs), so the tiles of a share meet in one
 // L2, or in few.  False past the last; the grid is wg_grid's.  Transposed 2x2,
@@ -1300,12 +1309,12 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_taps(WgradArgs a, int kb, in
   auto iterate = [&](Staged &g, bf16x8 (&An)[NA], const bf16x8 (&Ac)[NA], bool &real_n, bool real_c,
                      bf16x8 (&Bu)[MODE == 0 ? 3 : 1], const bf16x8 (&Bm)[MODE == 0 ? 3 : 1],
                      bf16x8 (&Bd)[MODE == 0 ? 3 : 1]) __attribute__((always_inline)) {
-    // LDS operations of a wave are done in order: these writes follow the
-    // last step's reads
+    wave_lds_fence();  // the last step's reads come first
     *reinterpret_cast<uint4 *>(sw + 16 * lane) = g.x;
     if (MODE == 0 && lane < 8) *reinterpret_cast<uint4 *>(sw + 16 * kPixBytes + 16 * lane) = g.xh;
 #pragma unroll
     for (int t = 0; t < NA; ++t) *reinterpret_cast<uint4 *>(sw + kDy + t * 16 * kPixBytes + 16 * lane) = g.dy[t];
+    wave_lds_fence();
     if (g.seg != pseg) {
       // columns outside the image read a zero pixel: their dy is zero, but zero
       // times an infinite x is not
