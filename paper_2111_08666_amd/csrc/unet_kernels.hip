@@ -31,6 +31,14 @@ __device__ __forceinline__ bf16x8 load8(const uint16_t *p) {
   const uint4 v = *reinterpret_cast<const uint4 *>(p);
   return __builtin_bit_cast(bf16x8, v);
 }
+// Eight channels at an address that need not be a multiple of 16 bytes (gfx950 reads and
+// writes such vectors in one instruction too; the type says that they may come).
+__device__ __forceinline__ uint4 load_any16(const uint16_t *p) {
+  uint4 v;
+  __builtin_memcpy(&v, p, sizeof v);
+  return v;
+}
+__device__ __forceinline__ void store_any16(uint16_t *p, const uint4 &v) { __builtin_memcpy(p, &v, sizeof v); }
 __device__ __forceinline__ bf16x8 zero8() { return __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0)); }
 __device__ __forceinline__ bf16x8 pack8(const uint16_t (&v)[8]) {
   uint4 u;
@@ -47,6 +55,11 @@ __device__ __forceinline__ bf16x8 pack8(const uint16_t (&v)[8]) {
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 constexpr uint32_t kWholeBuffer = 0x80000000u;  // bytes reachable from a base
 constexpr uint32_t kOutside = 0xc0000000u;      // offset of a masked lane (a scalar offset keeps it outside)
+// Buffer loads take multiples of four bytes; the kernels that load by plain addresses
+// serve other operands.
+static bool dword_aligned(const uint16_t *a, const uint16_t *b) {
+  return (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) % 4 == 0;
+}
 __device__ __forceinline__ uint4 buffer_load16(const uint16_t *base, uint32_t bytes, uint32_t offset) {
   // the caller's base is wave-uniform: say so, for a descriptor in scalar registers
   const uint64_t v = reinterpret_cast<uint64_t>(base);
@@ -897,6 +910,7 @@ static void launch_direct_tiles(const GemmArgs &a, int64_t P, hipStream_t s) {
 // offsets of a wave (its pixels, the rows above and below them) have to stay
 // within the buffer window, and its tiles within a grid.
 static bool direct_fits(const GemmArgs &a, int64_t P, int taps) {
+  if (!dword_aligned(a.x, a.wgt)) return false;
   if (reinterpret_cast<uintptr_t>(a.y) % 16 || a.y_cs % 8 || a.y_co % 8 || a.nout % 8) return false;
   if (a.act && (reinterpret_cast<uintptr_t>(a.act) % 16 || a.act_cs % 8 || a.act_co % 8)) return false;
   const int64_t reach = (taps == 9 ? 64 + 2 * (int64_t)a.w + 2 : 2 * (64 + 2 * (int64_t)a.w) * 2) * a.x_cs * 2;
@@ -1753,6 +1767,7 @@ static void launch_wgrad_gather(const WgradArgs &a, int kb, hipStream_t s) {
 //     as wide as x (64 -> 1024 at 16 x 33 x 100 162 / 211).
 template <int MODE>
 static bool gather_wins(const WgradArgs &a, int kb, bool rows) {
+  if (!dword_aligned(a.x, a.dy)) return true;
   const int64_t P = (int64_t)a.n * a.h * a.w, tiles = (int64_t)((a.cin + 31) / 32) * ((a.cout + 31) / 32);
   const int64_t blocks = kb * tiles;
   if (rows) return MODE == 0 ? P <= 128 : kb >= 3 && blocks >= 512 && 128 / a.w * a.w <= 96;
@@ -2003,10 +2018,8 @@ __global__ void relu_bwd_vec(const uint16_t *y, int64_t n_pix, int c8, int y_cs,
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t p = e / c8;
     const int ch = (int)(e - p * c8) * 8;
-    const uint4 yv = *reinterpret_cast<const uint4 *>(y + p * y_cs + y_co + ch);
-    uint4 *dp = reinterpret_cast<uint4 *>(dy + p * dy_cs + dy_co + ch);
-    const uint4 g = *dp;
-    *dp = relu_masked(g, yv);
+    uint16_t *const dp = dy + p * dy_cs + dy_co + ch;
+    store_any16(dp, relu_masked(load_any16(dp), load_any16(y + p * y_cs + y_co + ch)));
   }
 }
 
@@ -2043,7 +2056,7 @@ __device__ __forceinline__ float head_logit(const uint16_t *x, int64_t p, int c,
   float z = b;
   if ((c & 7) == 0 && (x_cs & 7) == 0) {  // 16-byte vectors of 8 channels
     for (int c8 = 0; c8 < c; c8 += 8) {
-      const uint4 v = *reinterpret_cast<const uint4 *>(x + p * x_cs + c8);
+      const uint4 v = load_any16(x + p * x_cs + c8);
       const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -2083,7 +2096,7 @@ __global__ void head_loss_pix(const uint16_t *x, int64_t n_pix, int c, int x_cs,
 #pragma unroll
         for (int k = 0; k < 4; ++k)
           u[k] = (uint32_t)f2bf(g * w[c8 + 2 * k]) | ((uint32_t)f2bf(g * w[c8 + 2 * k + 1]) << 16);
-        *reinterpret_cast<uint4 *>(dx + p * c + c8) = make_uint4(u[0], u[1], u[2], u[3]);
+        store_any16(dx + p * c + c8, make_uint4(u[0], u[1], u[2], u[3]));
       }
     } else if (dx) {
       for (int ch = 0; ch < c; ++ch) dx[p * c + ch] = f2bf(g * w[ch]);
@@ -2213,12 +2226,12 @@ __global__ void head_loss_sums_v(const uint16_t *x, int64_t n_pix, int c, int x_
     for (int i = 0; i < 8; ++i) {
       gv[i] = g[p + i * lanes];
       lv[i] = l[p + i * lanes];
-      v[i] = *reinterpret_cast<const uint4 *>(x + (p + i * lanes) * x_cs + cg * 8);
+      v[i] = load_any16(x + (p + i * lanes) * x_cs + cg * 8);
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) add(gv[i], lv[i], v[i]);
   }
-  for (; p < end; p += lanes) add(g[p], l[p], *reinterpret_cast<const uint4 *>(x + p * x_cs + cg * 8));
+  for (; p < end; p += lanes) add(g[p], l[p], load_any16(x + p * x_cs + cg * 8));
 #pragma unroll
   for (int j = 0; j < 8; ++j) red[threadIdx.x * 8 + j] = a[j];
   red_l[threadIdx.x] = sl;
