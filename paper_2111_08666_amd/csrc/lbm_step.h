@@ -1390,12 +1390,14 @@ __global__ __launch_bounds__(256) void cpsi_kernel(const InstDev *__restrict__ i
 }
 
 // The compacted D3Q19 collision walks backwards, from the populations that the
-// density pass has read last, where little of a state fits the Infinity Cache
-// (256 MiB); us per step by the size of the two population buffers (FP32 storage),
-// forwards / backwards: 269 MB (96^3 open box) 93.0 / 91.2, 405 MB (110^3) 130 / 133,
-// sphere packings of 128^3 (383 MB) 141 / 145, 160^3 (747 MB) 272 / 259 and 192^3
-// (1.3 GB) 445 / 433.  (Plain instead of streaming stores: 87 us for the 96^3 box
-// alone, but 3 % slower with three such states in flight.)
+// density pass has read last, where a state is much larger than the Infinity Cache
+// (256 MiB).  us per step of TRT, forwards / backwards, alone (three states in turn: the same
+// ratios), by the size of the two population buffers with FP32 storage in MB: open boxes 269 95.7 / 93.8,
+// 405 133.6 / 136.7, 499 182 / 168, 608 215 / 210, 834 286 / 277, 2152 675 / 659; sphere
+// packings 316 146 / 150, 414 190 / 180, 619 291 / 276, 1069 476 / 466, 1699 740 / 738.
+// From 560 MiB (587 MB) on it has won at every size.
+// (Plain instead of streaming stores: 87 us for the 96^3 box alone, but 3 % slower with
+// three such states in flight.)
 static bool collide_backwards(const InstDev &h, int q, int storage) {
   return q == 19 && storage == 0 && ((2 * 2 * 19 * 4 * (int64_t)h.cpitch) >> 20) >= 560;
 }

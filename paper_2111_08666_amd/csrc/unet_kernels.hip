@@ -1151,8 +1151,8 @@ __global__ __launch_bounds__(256) void wgrad_gather(WgradArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradients with all taps in one wave, for images of any width.  A wave owns a 32 x 32 tile of
-// (output, input) channels and marches down image rows, 16 pixels of a row
+// Weight gradients with all taps in one wave, for images of any width.  A wave owns a
+// 32 x 32 tile of (output, input) channels and marches down image rows, 16 pixels of a row
 // at a time, accumulating every tap of that tile: a row of x enters three
 // products per column shift (with the dy rows above, at and below it), so its
 // fragments stay in registers for three steps and an LDS read feeds more than
@@ -1164,7 +1164,8 @@ __global__ __launch_bounds__(256) void wgrad_gather(WgradArgs a) {
 //     zero row after every image (it supplies the zero row above and below;
 //     its own products are skipped).
 //   MODE 1, transposed 2x2: a step is 16 input pixels and their four dy pixels.
-// The eight waves of a block take consecutive step ranges and add their sums
+// The order of a sum is thus by segments of columns, then images and rows, in eight
+// ranges: the eight waves of a block take consecutive step ranges and add their sums
 // through LDS at the end, in wave order; a block writes one partial sum.
 // ---------------------------------------------------------------------------
 constexpr int kWgThreads = 512;  // eight waves
@@ -1422,11 +1423,13 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_taps(WgradArgs a, int kb, in
 
 // ---------------------------------------------------------------------------
 // Weight gradients in pixel order, for images of whole 16-pixel segments up to
-// 256 (MODE 1: 128) columns.  One accumulator takes a tap's products of 4096
-// pixels in the order they lie in memory, and the bias its pixel pairs, so a
-// gradient does not depend on how many waves shared the work (Adam's first steps
-// turn a last-place change of a vanishing gradient into a whole learning rate).
-// A block owns one such share of the pixels and a 32 x 32 channel tile.  Rows of
+// 256 (MODE 1: 128) columns.  One accumulator takes a tap's products of a share of the
+// pixels in the order they lie in memory, and the bias its pixel pairs.  Where the
+// width divides 4096 a share is 4096 pixels, as in wgrad_gather, whatever the number
+// of images, and the two give the same bits (Adam's first steps turn a last-place
+// change of a vanishing gradient into a whole learning rate); elsewhere it is
+// ceil(rows / shares) whole rows, with ceil(pixels / 4096) shares.
+// A block owns a share of the pixels and a 32 x 32 channel tile.  Rows of
 // x and dy go through LDS in stages of at most SP pixels, whole rows with a zero
 // column on both sides, x in a ring that also holds the rows above and below the
 // stage; a row outside its image is read from a block of zeros.
