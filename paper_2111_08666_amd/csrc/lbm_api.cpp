@@ -667,9 +667,12 @@ lbm_status create_batch(int32_t k, const lbm_geometry *g, const lbm_params *p,
   // not fit the L2), the fused step otherwise
   int strategy = resolve_strategy(g[0], p[0]);
   b->compact = compact_strategy(strategy);
-  int64_t tiles = 0;
-  for (int i = 0; i < k; ++i) tiles += (int64_t)((g[i].nx + kTileX - 1) / kTileX) * ((g[i].ny + 7) / 8);
-  const int default_rows = fused_rows(b->storage, b->math == LBM_MATH_F64, b->compact, tiles);
+  int64_t tiles = 0, nodes = 0;
+  for (int i = 0; i < k; ++i) {
+    tiles += (int64_t)((g[i].nx + kTileX - 1) / kTileX) * ((g[i].ny + 7) / 8);
+    nodes += (int64_t)g[i].nx * g[i].ny;
+  }
+  const int default_rows = fused_rows(b->collision, b->storage, b->math == LBM_MATH_F64, b->compact, tiles, nodes);
   const lbm_status ps = apply_plan(b, strategy, p[0].tile_rows ? p[0].tile_rows : default_rows);
   if (ps != LBM_OK) return ps;
   *out = owner.release();

@@ -22,29 +22,38 @@ constexpr uint32_t kLinkMask = (1u << 19) - 1u;
 constexpr int kTileX = 60;
 // Waves per block of the fused D2Q9 step: four, or eight with a row each for the 8-row
 // tile while waves are what is short (tiles: blocks of the launch, of 60 x 8 nodes; collision: as in
-// lbm.h).  us per step with four / eight waves:
-//   dense FP32: 182 tiles 8.9 / 7.8, 4250 73.0 / 70.7, 9400 152.2 / 154.2, 25125 390 / 404;
-//   dense FP64: 500 tiles 15.0 / 13.4, 1152 18.1 / 21.1, 9400 150 / 156;
-//   dense BF16: 500 tiles 16.1 / 14.2, 1152 22.3 / 22.2, 1350 24.6 / 25.3, 4250 54.4 / 61.6
-//     (MRT in FP64, of 256 registers with two rows: 1152 33.1 / 28.5, 25125 766 / 555);
-//   compacted FP64: 500 tiles 20.2 / 17.5, 2125 40.4 / 40.0, 4250 66.9 / 71.3.
+// lbm.h).  With eight, a state alone is faster up to a thousand tiles and more, but
+// where registers bind (FP64) or pulls are dear (BF16) several states in flight are slower from
+// 400 tiles on.  us per step with four / eight waves, one state; three in turn, each:
+//   dense FP32: 182 tiles 8.9 / 7.8; 4.2 / 3.5, 4250 73.0 / 70.7; 97 / 96, 9400 152.2 / 154.2;
+//   dense FP64 (TRT): 342 16.0 / 14.8; 6.0 / 5.4 (12 rows 17.0; 6.5), 600 17.4 / 16.2; 8.3 / 8.6,
+//     1152 18.1 / 21.1, 9400 150 / 156;
+//   dense BF16 (TRT): 342 13.9 / 12.6; 5.6 / 5.5 (12 rows 16.3; 6.2), 600 18.6 / 19.0; 7.2 / 8.7,
+//     980 21.3 / 20.6; 11.0 / 13.0 (MRT in FP64, of 256 registers with two rows: 1152 37 / 32; 27 / 23,
+//     9400 270 / 214; 267 / 218);
+//   compacted FP64 (TRT): 342 17.7 / 15.0; 7.2 / 6.3 (12 rows 22.7; 8.4), 600 22.2 / 22.2; 8.9 / 10.0,
+//     2125 42 / 42; 31 / 35.
 // The compacted FP32 and BF16 steps: lbm_step.h.
 constexpr int fused_waves(int ty, int collision, bool f64, int storage, bool compact, int64_t tiles) {
   const bool bf16 = storage != LBM_STORE_F32;
   if (ty != 8 || (compact && (!f64 || bf16))) return 4;
   if (bf16 && f64 && collision == 1) return 8;
-  return tiles <= (compact ? 3000 : bf16 ? 1280 : f64 ? 1024 : 6000) ? 8 : 4;
+  return tiles <= (f64 || bf16 ? 400 : 6000) ? 8 : 4;
 }
 // Tile height of the fused D2Q9 step when none is asked for (tiles: of 60 x 8 nodes,
-// all instances).  8 rows, but 12 where the pulls are the dearest per halo row and
-// waves are not what is short.  With BF16 storage: on the compacted layout (24
-// uneven instances: 109 us per step against 114 with 8), and on the dense one above
-// five tiles per CU (2648 tiles: 43 us against 47 with 8; 1472: 28 and 30;
-// 1064: 27 and 24; 24: 23 and 8.5).  With FP64 arithmetic on the compacted layout above
-// 3000 tiles (9400: 145 us against 152 with 8; 4250: 66.6 and 66.9; 2125: 41.9 and 41.2).
-constexpr int fused_rows(int storage, bool f64, bool compact, int64_t tiles) {
-  const bool bf16 = storage != LBM_STORE_F32;
-  return (bf16 && (compact || tiles > 1280)) || (f64 && compact && tiles > 3000) ? 12 : 8;
+// and nodes, of all instances).  8 rows, but 12 where the pulls are the dearest per halo row
+// and waves are not what is short; several states in flight get there before one does
+// (us per pass of 40 steps, three in flight, 12 / 8 rows; then us per step of one).
+//   BF16 storage, compacted layout: 24 uneven instances 109 us per step against 114.
+//   BF16 storage, dense, above five tiles per CU (one state, 2648 tiles: 43 and 47; 24: 23 and 8.5)
+//     or 320 000 nodes (700 x 400 302 / 285, 20.7 and 18.6; 800 x 480 353 / 375, 24.5 and 21.6),
+//     but for MRT in FP64, whose eight waves win there (1000 x 500 1024 / 903).
+//   FP64 arithmetic above 900 tiles (TRT, 600 x 400 324 / 292, 800 x 560 471 / 478, 1000 x 560
+//     642 / 710, one state 24.9 and 23.2 us), on the compacted layout above 800 (9400: 142 and 148).
+constexpr int fused_rows(int collision, int storage, bool f64, bool compact, int64_t tiles, int64_t nodes) {
+  if (storage != LBM_STORE_F32)
+    return compact || tiles > 1280 || (nodes > 320000 && !(f64 && collision == 1)) ? 12 : 8;
+  return f64 && tiles > (compact ? 800 : 900) ? 12 : 8;
 }
 // 3D step tile: the same 64-lane rows, TY3 interior rows in y, marching in z.
 constexpr int kTileY3 = 8;

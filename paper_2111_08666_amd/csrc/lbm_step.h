@@ -455,7 +455,7 @@ __device__ __forceinline__ void ccomplete9(const InstDev &d, gcf *__restrict__ f
 // 192 x 192 droplets 12.6 / 13.4 (15.3).  The compacted FP32 step keeps four
 // waves (24 uneven instances: 104.9 against 115.1 us): its rank lookups cost
 // more per row than the registers of a second row; in FP64 eight win there up
-// to 3000 tiles.
+// to 400 tiles.
 // (With the MRT collision's algebra in moments, since then: 1024 x 512 17.0,
 // 24 uneven instances 101.5.)
 // Four waves with TY = 12, and with TY = 8 in FP32, park the last interior row of
